@@ -15,16 +15,21 @@
 // computes a row, nor the other rows of the call reach its bits; only K (the
 // chain length and order) does, and there is no split over K.
 //
-// Launch: one workgroup of 8 wavefronts (4 x 2) per 256 x 192 output tile,
-// each wavefront a 64 x 96 part (4 x 6 MFMA blocks of 16 x 16).  K advances
-// in steps of 64 through a 2-stage LDS ring of A and B tiles (256 and 192
-// rows x 64 values; 112 KB, one workgroup and two wavefronts per SIMD on a
-// CU) filled by direct global-to-LDS copies, with one barrier per step; the 16-byte chunks of each
-// 128-byte LDS row are XOR-swizzled by the row so that the 16 rows one operand
-// read touches fall in different banks.  Tiles are taken in groups of 4 row
-// tiles sweeping the column tiles, and each XCD (workgroup id mod the die
-// count, 8 on a whole MI355X) takes a contiguous range of that order, so the A
-// and B panels of its workgroups are shared in its L2.
+// Launch: one workgroup per output tile, of one of the tile shapes below, the
+// shape chosen from M and N alone (run).  K advances in steps of BK values
+// through an LDS ring of ST stages of A and B tiles filled by direct
+// global-to-LDS copies, with one barrier per step; the 16-byte chunks of each
+// LDS row are XOR-swizzled by the row so that the 16 rows one operand read
+// touches fall in different banks.  Tiles are taken in groups of 4 row tiles
+// sweeping the column tiles, and each XCD (workgroup id mod the die count, 8 on
+// a whole MI355X) takes a contiguous range of that order, so the A and B
+// panels of its workgroups are shared in its L2.
+//
+// What bounds it: with few rows (decode), the weights from HBM (50 MB at
+// 4096 -> 6144: 7.9 us at the streaming rate) and, per workgroup, the chain of
+// steps -- copies, barrier, operand reads, dependent matrix instructions -- so
+// the small shapes take long steps (256 values) with up to 5 of them in
+// flight; with thousands of rows, the matrix cores (1.17 PFLOP/s at 4096 rows).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -37,44 +42,50 @@ using namespace vd;
 
 namespace {
 
-// Tile configuration: kWM x kWN wavefronts, each computing kXB x kYB MFMA
-// blocks of 16 x 16; K advances kBK per step (kBK / 32 MFMA chunks).  On the
-// Llama-3-8B QKV shape, 4 x 2 wavefronts of 4 x 6 blocks (a 256 x 192 tile,
-// one workgroup per CU) ran 9% faster than 2 x 2 wavefronts of 4 x 4 blocks
-// (128 x 128, two workgroups per CU), which beat 4 x 8 or 8 x 4 blocks per
-// wavefront at 4 wavefronts, 2 x 4 / 4 x 2 wavefronts of 4 x 4, 4 x 8 or
-// 8 x 4 blocks, and 192 x 256 tiles.
-constexpr int kWM = 4, kWN = 2;
-constexpr int kXB = 4, kYB = 6, kBK = 64;
-constexpr int kWaves = kWM * kWN;
-constexpr int kThreads = 64 * kWaves;
-constexpr int kBM = kWM * 16 * kXB;         // rows of a (tokens) per workgroup tile
-constexpr int kBN = kWN * 16 * kYB;         // rows of b (output features) per workgroup tile
-constexpr int kRowBytes = kBK * 2;          // one staged row of a tile
-constexpr int kChunks = kRowBytes / 16;     // 16-byte chunks per staged row
-constexpr int kRowsPerCopy = 1024 / kRowBytes;
-constexpr int kGroupM = 4;                  // row tiles per group of the tile order
-constexpr int kTileA = kBM * kRowBytes, kTileB = kBN * kRowBytes;
-constexpr int kStageBytes = kTileA + kTileB;
-constexpr int kLinLds = 2 * kStageBytes;    // 2-stage ring
-constexpr int kCopiesA = kTileA / 1024 / kWaves, kCopiesB = kTileB / 1024 / kWaves;  // per wavefront
-static_assert(kChunks == 4 || kChunks == 8, "staged rows of 64 or 128 bytes");
-static_assert(kCopiesA * 1024 * kWaves == kTileA && kCopiesB * 1024 * kWaves == kTileB,
-              "copy split");
+constexpr int kKStep = 64;  // K is a multiple of this
+constexpr int kGroupM = 4;  // row tiles per group of the tile order
 
-// Swizzle key of staged row r: chunk ch of the row sits in 16-byte slot
-// ch ^ key(r), so that 8 consecutive rows read at one chunk fill 8 distinct
-// 16-byte slots of a 128-byte bank window.
-__device__ __forceinline__ int swz_key(int r) {
-  return kChunks == 8 ? (r & 7) : ((r >> 1) & 3);
-}
-__device__ __forceinline__ int swz(int r, int ch) {
-  return r * kRowBytes + ((ch ^ swz_key(r)) << 4);
+// One tile shape: kWM x kWN wavefronts, each computing XB x YB MFMA blocks of
+// 16 x 16; K advances BK per step through an LDS ring of ST stages; EU is the
+// wavefronts per SIMD the registers are budgeted for.
+template <int WM_, int WN_, int XB_, int YB_, int BK_, int ST_, int EU_>
+struct Tile {
+  static constexpr int WM = WM_, WN = WN_, XB = XB_, YB = YB_, BK = BK_, ST = ST_, EU = EU_;
+  static constexpr int kWaves = WM * WN, kThreads = 64 * kWaves;
+  static constexpr int BM = WM * 16 * XB;         // rows of a (tokens) per workgroup tile
+  static constexpr int BN = WN * 16 * YB;         // rows of b (output features) per tile
+  static constexpr int kRowBytes = BK * 2;        // one staged row
+  static constexpr int kChunks = kRowBytes / 16;  // 16-byte chunks per staged row
+  static constexpr int kRowsPerCopy = 1024 / kRowBytes;
+  static constexpr int kTileA = BM * kRowBytes, kTileB = BN * kRowBytes;
+  static constexpr int kStage = kTileA + kTileB;
+  static constexpr int kLds = ST * kStage;
+  static constexpr int kCopiesA = kTileA / 1024, kCopiesB = kTileB / 1024;
+  static constexpr int kCopies = (kCopiesA + kCopiesB) / kWaves;  // per wavefront and stage
+  static_assert(kChunks >= 8 && kRowsPerCopy >= 1, "staged rows of 128 to 1024 bytes");
+  static_assert(kCopies * kWaves == kCopiesA + kCopiesB, "copy split");
+  static_assert((ST - 2) * kCopies < 64, "copies in flight within the wait counter");
+  static_assert(kLds <= 160 * 1024, "LDS of a compute unit");
+};
+
+// Waits until at most `later` stages of N copies each are outstanding.
+template <int N, int MAX>
+__device__ __forceinline__ void wait_stages(int later) {
+  if constexpr (MAX == 0) {
+    wait_vmcnt<0>();
+  } else {
+    if (later >= MAX)
+      wait_vmcnt<N * MAX>();
+    else
+      wait_stages<N, MAX - 1>(later);
+  }
 }
 
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void linear_kernel(
+template <class T>
+__global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::EU, T::EU))) void linear_kernel(
     const uint16_t* a, int64_t lda, const uint16_t* b, int64_t ldb, uint16_t* c, int64_t ldc,
     int64_t M, int N, int K, int tiles_m, int tiles_n, int xcd_shift) {
+  constexpr int XB = T::XB, YB = T::YB, BK = T::BK, ST = T::ST, CH = T::kChunks;
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   const int wave = uni(threadIdx.x >> 6);
   const int lane = __lane_id();
@@ -91,93 +102,182 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   const int64_t first_m = group * kGroupM;
   const int size_m = (int)((tiles_m - first_m) < kGroupM ? (tiles_m - first_m) : kGroupM);
   const int in_group = (int)(i - group * (int64_t)kGroupM * tiles_n);
-  const int64_t m0 = (first_m + in_group % size_m) * kBM;
-  const int n0 = (in_group / size_m) * kBN;
+  const int64_t m0 = (first_m + in_group % size_m) * T::BM;
+  const int n0 = (in_group / size_m) * T::BN;
 
-  // Copies: the staged A tile is kCopiesA * kWaves copies of 1 KB (kRowsPerCopy
-  // rows each), wavefront w taking copies w * kCopiesA + j; the same for B.
-  // Lane l of a copy carries row l / kChunks of it and 16-byte slot
-  // l % kChunks, i.e. source chunk slot ^ key(row) (the copy's first row is a
-  // multiple of kRowsPerCopy, so the key depends on the lane alone).  Rows
-  // past M (or N) repeat the last row: in bounds, and never stored.
-  const int lrow = lane / kChunks;
-  const int cch = (lane % kChunks) ^ swz_key(lrow);
-  const uint16_t* asrc[kCopiesA];
-  const uint16_t* bsrc[kCopiesB];
+  // Copies: a stage is kCopiesA copies of the A tile, then kCopiesB of the B
+  // tile, 1 KB (kRowsPerCopy rows) each; a wavefront takes kCopies of them, of
+  // each tile its even share where that divides.  Lane l of a copy carries
+  // row l / CH of it and 16-byte slot l % CH, i.e. source chunk slot ^ (row &
+  // 7), so that the 8 consecutive rows an operand read touches at one chunk
+  // lie in 8 distinct 16-byte slots of a 128-byte bank window.  Rows past M
+  // (or N) repeat the last row: in bounds, and never stored.
+  auto copy_of = [&](int j) {
+    constexpr bool even = T::kCopiesA % T::kWaves == 0 && T::kCopiesB % T::kWaves == 0;
+    constexpr int ca = T::kCopiesA / T::kWaves, cb = T::kCopiesB / T::kWaves;
+    if (!even) return wave * T::kCopies + j;
+    return j < ca ? wave * ca + j : T::kCopiesA + wave * cb + j - ca;
+  };
+  const uint16_t* src[T::kCopies];
+  int ck[T::kCopies];  // first k of the lane's chunk within the step
 #pragma unroll
-  for (int j = 0; j < kCopiesA; ++j) {
-    const int r = (wave * kCopiesA + j) * kRowsPerCopy + lrow;
-    const int64_t ra = m0 + r < M ? m0 + r : M - 1;
-    asrc[j] = a + ra * lda + 8 * cch;
-  }
-#pragma unroll
-  for (int j = 0; j < kCopiesB; ++j) {
-    const int r = (wave * kCopiesB + j) * kRowsPerCopy + lrow;
-    const int rb = n0 + r < N ? n0 + r : N - 1;
-    bsrc[j] = b + (int64_t)rb * ldb + 8 * cch;
+  for (int j = 0; j < T::kCopies; ++j) {
+    const int q = copy_of(j);
+    const bool is_a = q < T::kCopiesA;
+    const int r = (is_a ? q : q - T::kCopiesA) * T::kRowsPerCopy + lane / CH;
+    ck[j] = 8 * ((lane % CH) ^ (r & 7));
+    if (is_a) {
+      const int64_t ra = m0 + r < M ? m0 + r : M - 1;
+      src[j] = a + ra * lda;
+    } else {
+      const int rb = n0 + r < N ? n0 + r : N - 1;
+      src[j] = b + (int64_t)rb * ldb;
+    }
+    src[j] += ck[j];
   }
   const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
-  auto fetch = [&](int step, int buf) {
-    const int k0 = step * kBK;
-    const uint32_t st = lds0 + buf * kStageBytes;
+  const int steps = (K + BK - 1) / BK;
+  auto fetch = [&](int step) {
+    const int k0 = step * BK;
+    const uint32_t st = lds0 + (step % ST) * T::kStage;
+    if (BK == kKStep || k0 + BK <= K) {
 #pragma unroll
-    for (int j = 0; j < kCopiesA; ++j)
-      lds_dma16(asrc[j] + k0, uni((int)(st + 1024 * (wave * kCopiesA + j))));
+      for (int j = 0; j < T::kCopies; ++j)
+        lds_dma16(src[j] + k0, uni((int)(st + 1024 * copy_of(j))));
+    } else {
+      // the ragged last step: chunks past K repeat the row's last one (never used)
 #pragma unroll
-    for (int j = 0; j < kCopiesB; ++j)
-      lds_dma16(bsrc[j] + k0, uni((int)(st + kTileA + 1024 * (wave * kCopiesB + j))));
+      for (int j = 0; j < T::kCopies; ++j)
+        lds_dma16(src[j] - ck[j] + min(k0 + ck[j], K - 8), uni((int)(st + 1024 * copy_of(j))));
+    }
   };
 
-  // this wavefront's part: rows wm .. wm + 16 kXB - 1, columns wn .. wn + 16 kYB - 1
-  const int wm = 16 * kXB * (wave / kWN), wn = 16 * kYB * (wave % kWN);
+  // this wavefront's part: rows wm .. wm + 16 XB - 1, columns wn .. wn + 16 YB - 1
+  const int wm = 16 * XB * (wave / T::WN), wn = 16 * YB * (wave % T::WN);
   const int col = lane & 15, grp = lane >> 4;
-  f32x4 acc[kXB][kYB];
+  f32x4 acc[XB][YB];
 #pragma unroll
-  for (int x = 0; x < kXB; ++x)
+  for (int x = 0; x < XB; ++x)
 #pragma unroll
-    for (int y = 0; y < kYB; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int y = 0; y < YB; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // One barrier per step: after it, step t's copies are visible to every
   // wavefront and every wavefront is done with step t - 1, whose stage the
-  // copies of step t + 1 then refill while step t is computed.
-  const int steps = K / kBK;
-  if (steps > 0) fetch(0, 0);
+  // copies of step t + ST - 1 then refill while step t is computed.
+#pragma unroll
+  for (int t = 0; t < ST - 1; ++t)
+    if (t < steps) fetch(t);
   for (int t = 0; t < steps; ++t) {
-    wait_vmcnt<0>();  // this wavefront's copies of step t have landed
+    const int later = steps - 1 - t;
+    wait_stages<T::kCopies, ST - 2>(later);  // this wavefront's copies of step t have landed
     lds_barrier();
-    if (t + 1 < steps) fetch(t + 1, (t + 1) & 1);
-    const char* TA = reinterpret_cast<const char*>(lds) + (t & 1) * kStageBytes;
-    const char* TB = TA + kTileA;
-#pragma unroll
-    for (int kc = 0; kc < kBK / 32; ++kc) {
+    if (t + ST - 1 < steps) fetch(t + ST - 1);
+    const char* TA = reinterpret_cast<const char*>(lds) + (t % ST) * T::kStage;
+    const char* TB = TA + T::kTileA;
+    auto chunk = [&](int kc) {
       // operand of lane (col, grp): row col of the block, k = 32 kc + 8 grp .. + 7
-      u16x8 af[kXB], bf[kYB];
+      // (wm, wn and 16 x are multiples of 16, so the swizzle key is col & 7)
+      const int o = ((4 * kc + grp) ^ (col & 7)) << 4;
+      u16x8 af[XB], bf[YB];
 #pragma unroll
-      for (int x = 0; x < kXB; ++x)
-        af[x] = *reinterpret_cast<const u16x8*>(TA + swz(wm + 16 * x + col, 4 * kc + grp));
+      for (int x = 0; x < XB; ++x)
+        af[x] = *reinterpret_cast<const u16x8*>(TA + (wm + 16 * x + col) * T::kRowBytes + o);
 #pragma unroll
-      for (int y = 0; y < kYB; ++y)
-        bf[y] = *reinterpret_cast<const u16x8*>(TB + swz(wn + 16 * y + col, 4 * kc + grp));
+      for (int y = 0; y < YB; ++y)
+        bf[y] = *reinterpret_cast<const u16x8*>(TB + (wn + 16 * y + col) * T::kRowBytes + o);
 #pragma unroll
-      for (int x = 0; x < kXB; ++x)
+      for (int x = 0; x < XB; ++x)
 #pragma unroll
-        for (int y = 0; y < kYB; ++y) acc[x][y] = mfma(af[x], bf[y], acc[x][y]);
+        for (int y = 0; y < YB; ++y) acc[x][y] = mfma(af[x], bf[y], acc[x][y]);
+    };
+    if (BK == kKStep || (t + 1) * BK <= K) {
+#pragma unroll
+      for (int kc = 0; kc < BK / 32; ++kc) chunk(kc);
+    } else {
+      for (int kc = 0; kc < (K - t * BK) / 32; ++kc) chunk(kc);
     }
   }
 
   // accumulator cell i of block (x, y) in lane (col, grp): row 16 x + 4 grp + i, column 16 y + col
 #pragma unroll
-  for (int x = 0; x < kXB; ++x)
+  for (int x = 0; x < XB; ++x)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int64_t row = m0 + wm + 16 * x + 4 * grp + i;
       if (row >= M) continue;
 #pragma unroll
-      for (int y = 0; y < kYB; ++y) {
+      for (int y = 0; y < YB; ++y) {
         const int cn = n0 + wn + 16 * y + col;
         if (cn < N) c[row * ldc + cn] = bf16_rne(acc[x][y][i]);
       }
     }
+}
+
+struct Call {
+  const uint16_t *a, *b;
+  uint16_t* c;
+  int64_t lda, ldb, ldc, M;
+  int N, K;
+  hipStream_t stream;
+};
+
+template <class T>
+int launch(const Call& x) {
+  const int64_t tiles_m = (x.M + T::BM - 1) / T::BM, tiles_n = ((int64_t)x.N + T::BN - 1) / T::BN;
+  const Geometry geo = device_geometry();
+  const int64_t blocks = (tiles_m * tiles_n + geo.xcds - 1) / geo.xcds * geo.xcds;
+  if (tiles_m > INT32_MAX || blocks > INT32_MAX) return VD_ERR_INVALID_ARG;
+  static std::atomic<unsigned char> lds_set[kMaxDevices];
+  if (set_lds_limit(reinterpret_cast<const void*>(&linear_kernel<T>), T::kLds, lds_set) != hipSuccess)
+    return VD_ERR_LAUNCH;
+  hipLaunchKernelGGL(linear_kernel<T>, dim3((unsigned)blocks), dim3(T::kThreads), T::kLds, x.stream,
+                     x.a, x.lda, x.b, x.ldb, x.c, x.ldc, x.M, x.N, x.K, (int)tiles_m,
+                     (int)tiles_n, geo.xcd_shift);
+  return hipGetLastError() == hipSuccess ? VD_OK : VD_ERR_LAUNCH;
+}
+
+// The tile shapes, smallest first, each with the time of one round of its
+// tiles (a tile per CU of 256 at K = 4096, in us, kernel launches back to
+// back).  A call takes about ceil(tiles / CUs) rounds, so a shape that just
+// fills the chip wins over a larger one that leaves CUs idle and over a
+// smaller one that needs a second round or reads its operands more often.
+// Measured at K = 4096 (us; the 256 x 192 shape, used for every call before,
+// in brackets): 1 x 6144 12.0 [70.9], 32 x 6144 14.1 [71.7], 48 x 6144 16.6
+// [72.4], 100 x 6144 20.0 [74.4], 200 x 6144 23.3 [81.1], 300 x 6144 29.7
+// [75.6], 512 x 6144 37.6 [86.6], 1024 x 6144 52.8 [86.2], 4096 x 1024 38.6
+// [81.0], 2048 x 6144 (a full round) [93.4], 4096 x 6144 [177.0; 128 x 192
+// 203.8, 256 x 128 187.8, 256 x 256 182.5].
+#define VD_LINEAR_SHAPES(X)       \
+  X(1, 2, 1, 1, 256, 6, 1, 12.0f) \
+  X(2, 2, 1, 1, 256, 5, 1, 14.0f) \
+  X(1, 4, 1, 1, 256, 3, 1, 15.2f) \
+  X(4, 2, 1, 1, 256, 3, 1, 16.6f) \
+  X(2, 2, 2, 2, 64, 4, 2, 20.0f)  \
+  X(2, 2, 2, 3, 64, 4, 2, 23.5f)  \
+  X(2, 4, 2, 2, 64, 4, 2, 28.0f)  \
+  X(4, 4, 2, 2, 64, 4, 4, 37.5f)  \
+  X(4, 2, 2, 6, 64, 3, 2, 52.5f)  \
+  X(4, 2, 4, 6, 64, 2, 2, 88.0f)
+
+// The launch of the shape with the least rounds x time of a round.  The choice
+// never reaches a value (the arithmetic above).
+int run(const Call& x) {
+  const int cus = device_geometry().cus;
+  float best = 0.0f;
+  int (*fn)(const Call&) = nullptr;
+  auto consider = [&](int bm, int bn, float round_us, int (*f)(const Call&)) {
+    const int64_t tiles = ((x.M + bm - 1) / bm) * (((int64_t)x.N + bn - 1) / bn);
+    const float t = (float)((tiles + cus - 1) / cus) * round_us;
+    if (!fn || t < best) {
+      best = t;
+      fn = f;
+    }
+  };
+#define VD_LINEAR_CONSIDER(wm, wn, xb, yb, bk, st, eu, us) \
+  consider(16 * wm * xb, 16 * wn * yb, us, &launch<Tile<wm, wn, xb, yb, bk, st, eu>>);
+  VD_LINEAR_SHAPES(VD_LINEAR_CONSIDER)
+#undef VD_LINEAR_CONSIDER
+  return fn(x);
 }
 
 }  // namespace
@@ -187,24 +287,14 @@ extern "C" int vd_linear(const void* a, int64_t lda, const void* b, int64_t ldb,
   if (M < 0 || N < 0 || K < 0) return VD_ERR_INVALID_ARG;
   if (M == 0 || N == 0) return VD_OK;
   if (!c || ldc < N || (uintptr_t)c % 2 != 0) return VD_ERR_INVALID_ARG;
-  if (K % kBK != 0) return VD_ERR_UNSUPPORTED;
+  if (K % kKStep != 0) return VD_ERR_UNSUPPORTED;
   // a and b are read only when K > 0 (K = 0: every output is the empty sum, +0)
   if (K > 0) {
     if (!a || !b) return VD_ERR_INVALID_ARG;
     if (lda < K || ldb < K || lda % 8 != 0 || ldb % 8 != 0) return VD_ERR_INVALID_ARG;
     if (((uintptr_t)a | (uintptr_t)b) % 16 != 0) return VD_ERR_INVALID_ARG;
   }
-  const int64_t tiles_m = (M + kBM - 1) / kBM, tiles_n = ((int64_t)N + kBN - 1) / kBN;
-  const int64_t total = tiles_m * tiles_n;
-  const Geometry geo = device_geometry();
-  const int64_t blocks = (total + geo.xcds - 1) / geo.xcds * geo.xcds;
-  if (tiles_m > INT32_MAX || blocks > INT32_MAX) return VD_ERR_INVALID_ARG;
-  static std::atomic<unsigned char> lds_set[kMaxDevices];
-  if (set_lds_limit(reinterpret_cast<const void*>(&linear_kernel), kLinLds, lds_set) != hipSuccess)
-    return VD_ERR_LAUNCH;
-  hipLaunchKernelGGL(linear_kernel, dim3((unsigned)blocks), dim3(kThreads), kLinLds, stream,
-                     static_cast<const uint16_t*>(a), lda, static_cast<const uint16_t*>(b), ldb,
-                     static_cast<uint16_t*>(c), ldc, M, N, K, (int)tiles_m, (int)tiles_n,
-                     geo.xcd_shift);
-  return hipGetLastError() == hipSuccess ? VD_OK : VD_ERR_LAUNCH;
+  const Call x{static_cast<const uint16_t*>(a), static_cast<const uint16_t*>(b),
+               static_cast<uint16_t*>(c), lda, ldb, ldc, M, N, K, stream};
+  return run(x);
 }

@@ -147,3 +147,28 @@ def test_linear_random_shapes(case):
     assert np.array_equal(_gpu_linear(a, np.ascontiguousarray(b[cols])), got[:, cols])
     U.say("linear %dx%dx%d (lda %d): max abs err %.3g; %d rows and %d columns bit-identical" % (
         M, N, K, lda, err, len(sub), len(cols)))
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (15, 5000, 320),     # 16 x 32 tiles, a ragged last K step of 64
+    (31, 6100, 192),     # 32 x 32, K shorter than one step
+    (16, 16000, 448),    # 16 x 64, more tiles than a round of 16 x 32
+    (49, 6133, 576),     # 64 x 32
+    (97, 6140, 128),     # 64 x 64
+    (255, 6143, 192),    # 64 x 96
+    (511, 4090, 320),    # 64 x 128
+    (500, 6100, 64),     # 128 x 128
+    (1023, 6100, 128),   # 128 x 192
+    (2047, 6100, 192),   # 256 x 192
+])
+def test_linear_tile_shapes(M, N, K):
+    """A call of each tile shape on 256 CUs, ragged in M and N: sampled rows
+    within the bound of the oracle; the first, the last and a middle row alone
+    (another shape) and the last columns alone bit-identical."""
+    a, b = _draw(9000 + M, M, N, K)
+    got = _gpu_linear(a, b)
+    rows = [0, M // 2, M - 1]
+    _check_parity(a, b, got, rows=rows)
+    for x in rows:
+        assert np.array_equal(_gpu_linear(a[x:x + 1], b)[0], got[x]), x
+    assert np.array_equal(_gpu_linear(a, b[N - 37:]), got[:, N - 37:])
