@@ -23,12 +23,40 @@ def _gpu():
 @pytest.mark.parametrize("shape", [W.TINY, W.LLAMA8B], ids=["d64", "d128"])
 def test_kv_write_layout(shape):
     U.say("kv_write layout %s" % (shape,))
-    attn = U.handle(shape)
     rng = np.random.default_rng(5)
     num_pages, T = 37, 300
     slots = rng.choice(num_pages * 16, size=T, replace=False).astype(np.int64)
     slots[7] = -1  # skipped
     slots[9] = num_pages * 16 + 3  # out of range: skipped
+    check_kv_write(shape, rng, num_pages, slots)
+
+
+@pytest.mark.parametrize("shape", [W.TINY, W.LLAMA8B], ids=["d64", "d128"])
+@pytest.mark.parametrize("first", range(4))
+def test_kv_write_runs(shape, first):
+    """Runs of consecutive slots (1 to 70, started anywhere in a 4-slot group
+    and anywhere in a window of tokens), descending slots, skipped tokens inside
+    a run, a run past the pool's last slot and one from its first."""
+    rng = np.random.default_rng(50 + first)
+    num_pages = 60
+    last = num_pages * 16
+    runs = [np.arange(0, 5), np.arange(last - 6 + first, last + 3)]
+    at = 16 + first
+    for k in [1, 2, 3, 4, 5, 7, 8, 9, 16, 17, 70, 31, 64]:
+        runs.append(np.arange(at, at + k))
+        at += k + int(rng.integers(1, 6))
+    holes = np.arange(at, at + 40)
+    holes[[0, 5, 6, 13]] = -1
+    runs += [holes, np.arange(at + 60, at + 48, -1)]
+    order = rng.permutation(len(runs))
+    slots = np.concatenate([runs[i] for i in order]).astype(np.int64)
+    assert len(set(slots[slots >= 0])) == (slots >= 0).sum() and at + 60 < last - 6
+    check_kv_write(shape, rng, num_pages, slots)
+
+
+def check_kv_write(shape, rng, num_pages, slots):
+    attn = U.handle(shape)
+    T = len(slots)
     k = W.normal_bf16(rng, (T, shape.num_kv_heads, shape.head_dim))
     v = W.normal_bf16(rng, (T, shape.num_kv_heads, shape.head_dim))
     kp, vp = attn.new_pool(num_pages), attn.new_pool(num_pages)
