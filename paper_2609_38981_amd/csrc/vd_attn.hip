@@ -187,6 +187,16 @@ __device__ __forceinline__ void load_q(const Params& P, u16x8 (&qf)[D / 32], int
     qf[ks] = valid ? *reinterpret_cast<const u16x8*>(base + 32 * ks) : zero8();
 }
 
+// The Q operand of a 32-column block (vd_cas.hpp): lane l holds column l & 31.
+template <int D>
+__device__ __forceinline__ void load_q32(const Params& P, u16x8 (&qf)[D / 16], int tok, int head,
+                                         bool valid) {
+  const uint16_t* base = P.q + ((int64_t)tok * P.hq + head) * D + 8 * (__lane_id() >> 5);
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ++ks)
+    qf[ks] = valid ? *reinterpret_cast<const u16x8*>(base + 16 * ks) : zero8();
+}
+
 // Splits that hold a visible key of some row of request R: from the split of
 // the first row's window start through the split of key n - 1.  When it is
 // one, the split kernel writes the rows; otherwise the merge kernel does.
@@ -210,6 +220,25 @@ __device__ __forceinline__ void store_row(const Params& P, const f32x4 (&u)[D / 
     for (int i = 0; i < 4; ++i) v[i] = bf16_out(u[m][i] * rho);
     *reinterpret_cast<u16x4*>(o + 16 * m) = v;
   }
+}
+
+// The same from the accumulators of a 32-column block: d = 32 m + 8 (i / 4) + 4 hf + i % 4.
+template <int D>
+__device__ __forceinline__ void store_row32(const Params& P, const f32x16 (&u)[D / 32], float M,
+                                            float Z, int64_t tok, int head) {
+  const int hf = __lane_id() >> 5;
+  const float rho = final_scale(Z);
+  if (P.lse && hf == 0) P.lse[tok * P.hq + head] = final_lse(M, Z);
+  uint16_t* o = P.out + (tok * P.hq + head) * D + 4 * hf;
+#pragma unroll
+  for (int m = 0; m < D / 32; ++m)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      u16x4 v;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = bf16_out(u[m][4 * q + i] * rho);
+      *reinterpret_cast<u16x4*>(o + 32 * m + 8 * q) = v;
+    }
 }
 
 // Calls of at most this many requests find a row's request with one load of
@@ -1758,12 +1787,44 @@ __device__ __forceinline__ void order_pv_reads() {
   __builtin_amdgcn_sched_group_barrier(0x008, 4 * NB, 0);
 }
 
+// The same for the chunk kernel's 32 x 32 steps: four K reads, then one per
+// matrix instruction; the V reads of four steps, then two per step.  (8B mixed
+// batch, chunk kernel: 432 us with them, 467 without.)
+template <int D>
+__device__ __forceinline__ void order_qk_reads() {
+  constexpr int R = 2 * (D / 16), A = 4;
+  __builtin_amdgcn_sched_group_barrier(0x100, A, 0);
+#pragma unroll
+  for (int i = A; i < R; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+  }
+  __builtin_amdgcn_sched_group_barrier(0x008, A, 0);
+}
+template <int D>
+__device__ __forceinline__ void order_pv_reads() {
+  constexpr int R = 4 * (D / 32);  // steps, two V reads each
+  __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
+#pragma unroll
+  for (int i = 4; i < R; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+  }
+  __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+}
+
 // ---------------------------------------------------------------------------
 // chunk kernel: one workgroup (4 wavefronts x 32 columns) per
 // (request, KV head, 128 query-head rows).  The request's K/V tiles stream
 // through an LDS ring (kChunkStages tiles) filled by direct global-to-LDS
 // loads: while the wavefronts compute tile t, the loads of the next tiles are
-// in flight.  The splits are folded in registers as each one ends.
+// in flight.  The splits are folded in registers as each one ends.  The matrix
+// steps are 32 x 32 x 16 (vd_cas.hpp): the kernel is bound by the issue of its
+// matrix and vector instructions, and a 32 x 32 step holds up the vector issue
+// half as much per product.  With 16 x 16 x 32 steps (and the page ids read
+// where they are used, below) the 8B mixed batch's chunk kernel took 505 us,
+// now 433, a 512-token chunk at key 30000 806, now 670, four whole prompts of
+// 300 to 2000 tokens 67, now 62.
 // ---------------------------------------------------------------------------
 // Depth of the chunk kernel's LDS ring: tiles t + 1 .. t + kChunkStages - 1 are
 // in flight while tile t is computed.
@@ -1800,7 +1861,6 @@ __device__ __forceinline__ void load_pid_window(const Params& P, const int32_t* 
 // compiles away (the kernel is at its register budget).
 template <int D, bool WIN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void chunk_kernel(Params P) {
-  constexpr int NB = 2;
   constexpr int BLK = kPage * D;                   // elements of one page block
   constexpr int NBLK = 2 * kPagesPerTile;          // 4 K blocks then 4 V blocks
   constexpr int TILE = NBLK * BLK;                 // elements of one staged tile
@@ -1809,7 +1869,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];  // [STAGES][NBLK][BLK]
   const int wave = uni(threadIdx.x >> 6);
   const int lane = __lane_id();
-  const int col = lane & 15;
+  const int col = lane & 31, hf = lane >> 5;
   const int window = WIN ? P.window : 0;
   // Items are ordered (KV head, request, q-tile) and blocks of one XCD (block
   // id mod the die count) take a contiguous range of them: the q-tiles of one
@@ -1839,27 +1899,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int cend = min(ncols, c0 + kChunkCols);
   const int pmax = R.n - R.s + (cend - 1) / P.G;  // last position of the block
 
-  int pos[NB], lo[NB];  // visible keys of the column: lo .. pos
-  u16x8 qf[NB][D / 32];
-  State<D> st[NB];
-  float M[NB], Z[NB];
-  f32x4 W[NB][D / 16];
-  int wave_pmax = -1;
+  // this lane's column, and its visible keys: lo .. pos
+  const int c = c0 + wave * 32 + col;
+  const bool live = c < cend;
+  const int pos = live ? R.n - R.s + c / P.G : -1;
+  const int lo = window_lo(pos, window);
+  u16x8 qf[D / 16];
+  load_q32<D>(P, qf, R.q0 + (live ? c / P.G : 0), g * P.G + (live ? c % P.G : 0), live);
+  State32<D> st;
+  float M = 0.f, Z = 0.f;
+  f32x16 W[D / 32];
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    const int c = c0 + wave * 32 + nb * 16 + col;
-    const bool v = c < cend;
-    pos[nb] = v ? R.n - R.s + c / P.G : -1;
-    lo[nb] = window_lo(pos[nb], window);
-    load_q<D>(P, qf[nb], R.q0 + (v ? c / P.G : 0), g * P.G + (v ? c % P.G : 0), v);
-    const int cb = c0 + wave * 32 + nb * 16;
-    const int clast = min(cend, cb + 16) - 1;
-    if (clast >= cb) wave_pmax = max(wave_pmax, R.n - R.s + clast / P.G);
-    M[nb] = 0.f;
-    Z[nb] = 0.f;
-#pragma unroll
-    for (int m = 0; m < D / 16; ++m) W[nb][m] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+  for (int m = 0; m < D / 32; ++m) W[m] = f32x16{};
+  // last position of this wavefront's columns (-1: none)
+  const int wave_c1 = min(cend, c0 + wave * 32 + 32) - 1;
+  const int wave_pmax = wave_c1 >= c0 + wave * 32 ? R.n - R.s + wave_c1 / P.G : -1;
 
   const int32_t* ptrow = P.pt + (int64_t)r * P.pt_stride;
   const int ntiles = pmax / kTileKeys + 1;
@@ -1878,39 +1932,37 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     bad = bad || pg < 0 || pg >= P.num_pages;
   }
   const bool pages_ok = !__any(bad);
-  // The page blocks of tile kt (-1: past the request's pages or outside the
-  // pool); a tile below the request's last page takes its 4 table entries in
-  // one scalar load.
-  auto tile_blocks = [&](int kt, int64_t (&pb)[kPagesPerTile]) {
-    const int lp0 = kt * kPagesPerTile;
-    if (lp0 + kPagesPerTile <= npages) {
-      typedef __attribute__((address_space(4))) const int32_t const_i32;
-      const const_i32* e = (const const_i32*)(ptrow + lp0);
-      const int32_t pg[kPagesPerTile] = {e[0], e[1], e[2], e[3]};
+  // This wavefront's WCH direct loads of a tile: NP whole page blocks of its 4
+  // K and 4 V blocks, from block blk0 (SUBS 1 KB parts of a block share one M0
+  // setting).  In LDS the two 128-byte runs {slots 0-3, 4-7} and {8-11, 12-15}
+  // of every odd group of 16 d of a V block change places, so that the 32
+  // lanes of half a V operand read touch distinct banks.
+  constexpr int SUBS = BLK / 512;
+  constexpr int NP = WCH / SUBS;
+  static_assert(WCH % SUBS == 0 && kPagesPerTile % NP == 0, "whole page blocks per wavefront");
+  const int blk0 = wave * NP;
+  const bool copies_v = blk0 >= kPagesPerTile;
+  const uint16_t* pool = (copies_v ? P.vpool : P.kpool) + (int64_t)g * BLK +
+                         8 * (copies_v ? lane ^ ((lane >> 5) << 3) : lane);
+  const int64_t page_elems = (int64_t)P.hkv * BLK;
+  // The page ids of a tile's copies are read one tile ahead (scalar loads that
+  // return during the wait for the copies in flight), from entries clamped to
+  // the request's pages.  Read where they were used, four dependent loads a
+  // tile held up the copies: 806 against 723 us for a 512-token chunk at key
+  // 30000 (one request), 499 against 476 us for the 8B mixed batch.
+  int ids[NP];
+  auto load_ids = [&](int kt) {
+    typedef __attribute__((address_space(4))) const int32_t const_i32;
 #pragma unroll
-      for (int b = 0; b < kPagesPerTile; ++b)
-        pb[b] = (pg[b] < 0 || pg[b] >= P.num_pages) ? -1 : (int64_t)pg[b] * P.hkv + g;
-    } else {
-#pragma unroll
-      for (int b = 0; b < kPagesPerTile; ++b) pb[b] = page_block(P, ptrow, lp0 + b, R.n, g);
-    }
+    for (int i = 0; i < NP; ++i)
+      ids[i] = ((const const_i32*)ptrow)[min(kt * kPagesPerTile + blk0 % kPagesPerTile + i, npages - 1)];
   };
-  // Issues this wavefront's WCH direct loads of tile kt into stage buf: copy
-  // q = wave * WCH + w moves 1 KB of page block q / (BLK / 512); a wavefront's
-  // copies cover whole page blocks, whose 1 KB parts share one M0 setting.
-  constexpr int SUBS = BLK / 512;  // 1 KB copies per page block
-  static_assert(WCH % SUBS == 0, "whole page blocks per wavefront");
-  auto fetch = [&](int kt, int buf) {
-    int64_t pb[kPagesPerTile];
-    tile_blocks(kt, pb);
+  auto fetch = [&](int buf) {
 #pragma unroll
-    for (int w = 0; w < WCH; w += SUBS) {
-      const int blk = (wave * WCH + w) / SUBS;
-      const int b = blk % kPagesPerTile;
-      const int64_t pbb = pb[b] < 0 ? 0 : pb[b];
-      const uint16_t* src = block_ptr<D>(blk < kPagesPerTile ? P.kpool : P.vpool, pbb) + 8 * lane;
-      const uint32_t dst = (uint32_t)(uintptr_t)(lds + (buf * NBLK + blk) * BLK);
-      lds_dma16_run<SUBS>(src, uni((int)dst));
+    for (int i = 0; i < NP; ++i) {
+      const int page = (unsigned)ids[i] < (unsigned)P.num_pages ? ids[i] : 0;
+      const uint32_t dst = (uint32_t)(uintptr_t)(lds + (buf * NBLK + blk0 + i) * BLK);
+      lds_dma16_run<SUBS>(pool + page * page_elems, uni((int)dst));
     }
   };
   // Zeroes, in stage buf, the K rows and V entries of keys >= n or of
@@ -1932,7 +1984,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const int slot = (off / 8) % 16;  // K block: [D/8][16][8]
         if (!pok || kbase + slot >= R.n) v = zero8();
       } else {
-        const int sg = (off / 64) % 4;  // V block: [D/16][4][16][4]
+        const int sg = (off / 64) % 4 ^ ((off / 256) & 1);  // V block: [D/16][4][16][4], runs as above
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = (pok && kbase + 4 * sg + (e % 4) < R.n) ? v[e] : (uint16_t)0;
       }
@@ -1951,7 +2003,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   wait_vmcnt<0>();  // the Q operands are in registers before any tile copy is issued
 #pragma unroll
   for (int t = 0; t < STAGES - 1; ++t)
-    if (kt_first + t < ntiles) fetch(kt_first + t, (kt_first + t) % STAGES);
+    if (kt_first + t < ntiles) {
+      load_ids(kt_first + t);
+      fetch((kt_first + t) % STAGES);
+    }
+  load_ids(kt_first + STAGES - 1);
   for (int kt = kt_first; kt < ntiles; ++kt) {
     const int j0 = kt * kTileKeys;
     const int k = kt / kTilesPerSplit;
@@ -1972,82 +2028,66 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       mask_stage(kt, buf);
       lds_barrier();
     }
-    if (kt + STAGES - 1 < ntiles) fetch(kt + STAGES - 1, (kt + STAGES - 1) % STAGES);
-    if (kt % kTilesPerSplit == 0 || kt == kt_first) {
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) state_init(st[nb]);
-    }
+    if (kt + STAGES - 1 < ntiles) fetch((kt + STAGES - 1) % STAGES);
+    if (kt % kTilesPerSplit == 0 || kt == kt_first) state32_init(st);
     const uint16_t* T = lds + buf * NBLK * BLK;
     if (wave_pmax >= j0 && j0 + kTileKeys - 1 >= wave_lo) {
-      f32x4 acc[NB][kPagesPerTile];
+      f32x16 acc[2];
       // The two wavefronts of a SIMD belong to different workgroups; the one
       // issuing matrix-core work gets the higher issue priority, the other's
       // softmax fills the vector ALU around it.
       __builtin_amdgcn_s_setprio(2);
-      tile_scores<D, NB>(
-          [&](int b, int ks) { return *reinterpret_cast<const u16x8*>(T + b * BLK + 512 * ks + 8 * lane); },
+      // key 32 b + col: page 2 b + col / 16, slot col % 16
+      const uint16_t* TK = T + (col / 16) * BLK + 128 * hf + 8 * (col % 16);
+      tile_scores32<D>(
+          [&](int b, int ks) { return *reinterpret_cast<const u16x8*>(TK + 2 * b * BLK + 256 * ks); },
           qf, acc);
-      order_qk_reads<D, NB>();
+      order_qk_reads<D>();
       __builtin_amdgcn_s_setprio(0);
-      TileWeights w[NB];
-      bool open = true;  // every key of the tile visible to every column
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-        open = open && __all(pos[nb] >= j0 + kTileKeys - 1 && lo[nb] <= j0);
-      if (open) {
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-          w[nb] = tile_softmax<D, false, WIN>(st[nb], acc[nb], j0, pos[nb], lo[nb], P.c);
-      } else {
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-          w[nb] = tile_softmax<D, true, WIN>(st[nb], acc[nb], j0, pos[nb], lo[nb], P.c);
-      }
+      // every key of the tile visible to every column
+      const bool open = __all(pos >= j0 + kTileKeys - 1 && lo <= j0);
+      TileWeights32 w;
+      if (open)
+        w = tile_softmax32<false, WIN>(st.m, st.z, acc, j0, pos, lo, P.c);
+      else
+        w = tile_softmax32<true, WIN>(st.m, st.z, acc, j0, pos, lo, P.c);
       __builtin_amdgcn_s_setprio(2);
+      // d 32 m + col, slots 4 (hf + 2 y) .. + 3 of the pages 2 b and 2 b + 1
+      const uint16_t* TV = T + kPagesPerTile * BLK + 256 * (col / 16) + 64 * (hf ^ (col / 16)) + 4 * (col % 16);
 #pragma unroll
-      for (int m = 0; m < D / 16; ++m) {
-        const int o = 256 * m + 4 * lane;
-        const u16x8 v0 = cat4(lds_read8<u16x4>(T + 4 * BLK + o), lds_read8<u16x4>(T + 5 * BLK + o));
-        const u16x8 v1 = cat4(lds_read8<u16x4>(T + 6 * BLK + o), lds_read8<u16x4>(T + 7 * BLK + o));
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) tile_pv_block<D>(st[nb], w[nb], m, v0, v1);
-      }
-      order_pv_reads<D, NB>();
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) tile_commit<D>(st[nb], w[nb]);
+      for (int m = 0; m < D / 32; ++m)
+        tile_pv_block32<D>(st, w, m, [&](int x) {
+          const uint16_t* v = TV + 2 * (x / 2) * BLK + 128 * (x % 2) + 512 * m;
+          return cat4(lds_read8<u16x4>(v), lds_read8<u16x4>(v + BLK));
+        });
+      order_pv_reads<D>();
+      tile_commit32<D>(st, w);
       __builtin_amdgcn_s_setprio(0);
     }
+    load_ids(kt + STAGES);
     if (kt % kTilesPerSplit == kTilesPerSplit - 1 || kt == ntiles - 1) {
       // split k ends: fold it into the running merge for columns that have it
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        // the column's splits run from the one holding its window start
-        const int klo = lo[nb] / kSplitKeys;
-        if (pos[nb] < 0 || k > pos[nb] / kSplitKeys || k < klo) continue;
+      // (a column's splits run from the one holding its window start)
+      const int klo = lo / kSplitKeys;
+      if (pos >= 0 && k <= pos / kSplitKeys && k >= klo) {
         if (k == klo) {
-          M[nb] = st[nb].m;
-          Z[nb] = st[nb].z;
+          M = st.m;
+          Z = st.z;
 #pragma unroll
-          for (int m = 0; m < D / 16; ++m) W[nb][m] = st[nb].u[m];
+          for (int m = 0; m < D / 32; ++m) W[m] = st.u[m];
         } else {
-          const FoldScalars f = fold_scalars(M[nb], Z[nb], st[nb].m, st[nb].z);
+          const FoldScalars f = fold_scalars(M, Z, st.m, st.z);
 #pragma unroll
-          for (int m = 0; m < D / 16; ++m)
+          for (int m = 0; m < D / 32; ++m)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) W[nb][m][e] = fold_value(W[nb][m][e], st[nb].u[m][e], f);
-          M[nb] = f.M;
-          Z[nb] = f.Z;
+            for (int e = 0; e < 16; ++e) W[m][e] = fold_value(W[m][e], st.u[m][e], f);
+          M = f.M;
+          Z = f.Z;
         }
       }
     }
   }
-
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    if (pos[nb] < 0) continue;
-    const int c = c0 + wave * 32 + nb * 16 + col;
-    store_row<D>(P, W[nb], M[nb], Z[nb], R.q0 + c / P.G, g * P.G + c % P.G);
-  }
+  if (live) store_row32<D>(P, W, M, Z, R.q0 + c / P.G, g * P.G + c % P.G);
 }
 
 // Dynamic LDS bytes of the chunk kernel: kChunkStages stages of 8 page blocks.

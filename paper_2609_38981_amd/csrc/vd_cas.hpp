@@ -47,6 +47,7 @@ constexpr int kChunkCols = 128; // query-head rows per work item on the chunk pa
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
 typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
 
@@ -81,12 +82,14 @@ __device__ __forceinline__ float fmax_(float a, float b) { return __builtin_fmax
 // half) of every pair of lanes l, l ^ 16 (l, l ^ 32) and the second the odd
 // row (upper half).  The two wait states before each swap are its hazard
 // after a vector-ALU write of either register.  Every lane of the wavefront
-// must be active (the callers' tile loops are wave-uniform).
+// must be active (the callers' tile loops are wave-uniform).  Not volatile: the
+// results depend on the two registers alone, and a volatile statement would
+// keep the compiler from scheduling LDS reads across the softmax.
 __device__ __forceinline__ void swap_rows16(float& a, float& b) {
-  asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+  asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
 }
 __device__ __forceinline__ void swap_rows32(float& a, float& b) {
-  asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+  asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
 }
 
 // The maximum (sum) over the four lanes of a column, l, l ^ 16, l ^ 32 and
@@ -244,6 +247,144 @@ __device__ __forceinline__ void tile_pv_block(State<D>& st, const TileWeights& w
 // (m, z) <- select(h, new, old)
 template <int D>
 __device__ __forceinline__ void tile_commit(State<D>& st, const TileWeights& w) {
+  st.m = w.h ? w.m_new : st.m;
+  st.z = w.h ? w.z_new : st.z;
+}
+
+// ---------------------------------------------------------------------------
+// The same update on v_mfma_f32_32x32x16_bf16, for a wavefront with 32 columns
+// (chunk and shared-prefix kernels).  One 16x16x32 step equals two chained
+// 32x32x16 steps, over operand elements k = 0..15 and then 16..31, in every
+// cell and bit (a probe on gfx950 pins it), so each dot product runs as a chain
+// of 32x32x16 steps in the same k order.  A 32x32x16 step keeps the matrix core
+// busy for 32 cycles and the vector issue for 8 of them, where the two
+// 16x16x32 steps it replaces take 16 and 8 each: twice the issue slots are left
+// to the softmax.  A column lies in two lanes (l, l ^ 32) instead of four.
+//
+// Wavefront layout of one 32-column block (lane l, col = l & 31, hf = l >> 5):
+//   Q operand (B of Q.K, chunk ks):   q[col][16 ks + 8 hf + j], j = 0..7
+//   K operand (A, key block B, ks):   K[key 32 B + col][16 ks + 8 hf + j]
+//   score accumulator of key block B: S[key 32 B + 8 (i / 4) + 4 hf + i % 4][col], i = 0..15
+//   P operand (B of P.V, step x = 2 B + y): slot j <-> key 32 B + 8 y + 16 (j / 4) + 4 hf + j % 4
+//   V operand (A, d-block m, step x):       V[that key][32 m + col]
+//   U accumulator of d-block m:             U[32 m + 8 (i / 4) + 4 hf + i % 4][col]
+// Step x = 2 B + y holds the elements k = 16 y .. 16 y + 15 of the 16x16x32
+// step of key half B: its lane groups 2 y and 2 y + 1.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ f32x16 mfma32(const u16x8& a, const u16x8& b, const f32x16& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// Online-softmax state of the lane's column (replicated in its two lanes).
+template <int D>
+struct State32 {
+  float m, z;
+  f32x16 u[D / 32];
+};
+
+template <int D>
+__device__ __forceinline__ void state32_init(State32<D>& st) {
+  st.m = -__builtin_inff();
+  st.z = 0.0f;
+#pragma unroll
+  for (int b = 0; b < D / 32; ++b)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) st.u[b][i] = 0.0f;
+}
+
+// Score blocks of one tile; kf(B, ks) yields the K operand of key block B.
+template <int D, class KF>
+__device__ __forceinline__ void tile_scores32(const KF& kf, const u16x8 (&qf)[D / 16],
+                                              f32x16 (&acc)[2]) {
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[b][i] = 0.0f;
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ++ks)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) acc[b] = mfma32(kf(b, ks), qf[ks], acc[b]);
+}
+
+struct TileWeights32 {
+  u16x8 pf[4];
+  float alpha, m_new, z_new;
+  uint32_t h;
+};
+
+// tile_softmax on the 32-column layout: the same operations per column.  The
+// sum's tree (the lane's cells of one old lane group, then the groups 0 + 1 and
+// 2 + 3, then both) keeps its operands: this lane holds the groups hf and hf +
+// 2, cells with i / 4 even and odd.
+template <bool MASKED = true, bool WIN = true>
+__device__ __forceinline__ TileWeights32 tile_softmax32(float m, float z, const f32x16 (&acc)[2],
+                                                        int j0, int p, int lo, float c) {
+  const int hf = __lane_id() >> 5;
+  float g[2][16];
+  bool lam[2][16];
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int key = j0 + 32 * b + 8 * (i / 4) + 4 * hf + i % 4;
+      lam[b][i] = !MASKED || (key <= p && (!WIN || key >= lo));
+      g[b][i] = acc[b][i] * c;
+    }
+  float mx = -__builtin_inff();
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) mx = fmax_(mx, lam[b][i] ? g[b][i] : -__builtin_inff());
+  {
+    float o = mx;
+    swap_rows32(mx, o);
+    mx = fmax_(mx, o);
+  }
+  TileWeights32 w;
+  w.h = !MASKED || (j0 <= p && (!WIN || j0 + kTileKeys - 1 >= lo));
+  w.m_new = fmax_(m, mx);
+  w.alpha = w.h ? ex2(m - w.m_new) : 1.0f;  // a column with no visible key: see tile_softmax
+  float a[2][16];
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) a[b][i] = lam[b][i] ? ex2(g[b][i] - w.m_new) : 0.0f;
+  // page 2 b + pg of the tile, lane group hf + 2 par: cells 8 pg + 4 par .. + 3
+  float s[2];
+#pragma unroll
+  for (int par = 0; par < 2; ++par) {
+    float sb[4];
+#pragma unroll
+    for (int pgi = 0; pgi < 4; ++pgi) {
+      const int b = pgi / 2, i = 8 * (pgi % 2) + 4 * par;
+      sb[pgi] = (a[b][i] + a[b][i + 1]) + (a[b][i + 2] + a[b][i + 3]);
+    }
+    s[par] = (sb[0] + sb[1]) + (sb[2] + sb[3]);
+  }
+  swap_rows32(s[0], s[1]);  // lower half: groups 0, 1; upper half: groups 2, 3
+  float sum = s[0] + s[1], other = sum;
+  swap_rows32(sum, other);
+  w.z_new = z * w.alpha + (sum + other);
+#pragma unroll
+  for (int x = 0; x < 4; ++x)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) w.pf[x][j] = bf16_rne(a[x / 2][8 * (j / 4) + 4 * (x % 2) + j % 4]);
+  return w;
+}
+
+// P.V for the 32-d block m: vf(x) yields the V operand of step x.
+template <int D, class VF>
+__device__ __forceinline__ void tile_pv_block32(State32<D>& st, const TileWeights32& w, int m,
+                                                const VF& vf) {
+  f32x16 u = st.u[m] * w.alpha;
+#pragma unroll
+  for (int x = 0; x < 4; ++x) u = mfma32(vf(x), w.pf[x], u);
+  st.u[m] = u;
+}
+
+template <int D>
+__device__ __forceinline__ void tile_commit32(State32<D>& st, const TileWeights32& w) {
   st.m = w.h ? w.m_new : st.m;
   st.z = w.h ? w.z_new : st.z;
 }

@@ -30,6 +30,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
 
 // Operand layout of the instruction (the one the attention kernels use):
@@ -54,6 +55,32 @@ __global__ __launch_bounds__(64) void mfma_tile_kernel(const uint16_t* a, const 
   acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av),
                                                 __builtin_bit_cast(bf16x8, bv), acc, 0, 0, 0);
   for (int i = 0; i < 4; ++i) dt[(4 * g + i) * 16 + r] = acc[i];
+}
+
+// Two chained v_mfma_f32_32x32x16_bf16 over k = 0..15 and 16..31 of a 32 x 32
+// tile: lane l holds A[l % 32][8 (l / 32) + e], B[8 (l / 32) + e][l % 32] (plus 16
+// in k for the second), and D[8 (i / 4) + 4 (l / 32) + i % 4][l % 32], i = 0..15.
+__global__ __launch_bounds__(64) void mfma32_tile_kernel(const uint16_t* a, const uint16_t* b,
+                                                         const float* c, float* d, int tiles) {
+  const int t = blockIdx.x;
+  if (t >= tiles) return;
+  const int l = threadIdx.x, r = l % 32, g = l / 32;
+  const uint16_t* at = a + (int64_t)t * 1024;
+  const uint16_t* bt = b + (int64_t)t * 1024;
+  const float* ct = c + (int64_t)t * 1024;
+  float* dt = d + (int64_t)t * 1024;
+  f32x16 acc;
+  for (int i = 0; i < 16; ++i) acc[i] = ct[(8 * (i / 4) + 4 * g + i % 4) * 32 + r];
+  for (int h = 0; h < 2; ++h) {
+    u16x8 av, bv;
+    for (int e = 0; e < 8; ++e) {
+      av[e] = at[r * 32 + 16 * h + 8 * g + e];
+      bv[e] = bt[(16 * h + 8 * g + e) * 32 + r];
+    }
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av),
+                                                  __builtin_bit_cast(bf16x8, bv), acc, 0, 0, 0);
+  }
+  for (int i = 0; i < 16; ++i) dt[(8 * (i / 4) + 4 * g + i % 4) * 32 + r] = acc[i];
 }
 
 __global__ __launch_bounds__(64) void exp2_kernel(const float* x, float* y, int64_t n) {
@@ -103,6 +130,16 @@ int vdp_mfma_bf16(const void* a, const void* b, const void* c, void* d, int tile
   if (tiles < 0 || (tiles > 0 && (!a || !b || !c || !d))) return -1;
   if (tiles == 0) return 0;
   hipLaunchKernelGGL(mfma_tile_kernel, dim3((unsigned)tiles), dim3(64), 0, stream,
+                     static_cast<const uint16_t*>(a), static_cast<const uint16_t*>(b),
+                     static_cast<const float*>(c), static_cast<float*>(d), tiles);
+  return launched();
+}
+
+int vdp_mfma32_bf16(const void* a, const void* b, const void* c, void* d, int tiles,
+                    hipStream_t stream) {
+  if (tiles < 0 || (tiles > 0 && (!a || !b || !c || !d))) return -1;
+  if (tiles == 0) return 0;
+  hipLaunchKernelGGL(mfma32_tile_kernel, dim3((unsigned)tiles), dim3(64), 0, stream,
                      static_cast<const uint16_t*>(a), static_cast<const uint16_t*>(b),
                      static_cast<const float*>(c), static_cast<float*>(d), tiles);
   return launched();

@@ -12,6 +12,9 @@ built by __graft_entry__.build()) and checking their results on the host.
   issues the same matrix instruction as prefill instead of a vector-ALU dot
   product (the paper's Section 5.3 contract: one operation sequence per
   logical position, whatever the query length).
+* v_mfma_f32_32x32x16_bf16: two of them chained, over k = 0..15 and 16..31,
+  give every cell the bits of one v_mfma_f32_16x16x32_bf16 -- the chunk kernel
+  runs its dot products as 32 x 32 steps, the split kernel as 16 x 16 ones.
 * v_exp_f32: exp2(+-0) = 1, exp2(-inf) = 0 (the identity and masked steps of
   the softmax), and results below the normal range are flushed to +0.
 * v_cvt_pk_bf16_f32: round to nearest, ties to even (the P operand's cast).
@@ -47,11 +50,12 @@ def probes():
     lib = ctypes.CDLL(LIB)
     vp = ctypes.c_void_p
     lib.vdp_mfma_bf16.argtypes = [vp, vp, vp, vp, ctypes.c_int, vp]
+    lib.vdp_mfma32_bf16.argtypes = lib.vdp_mfma_bf16.argtypes
     lib.vdp_exp2.argtypes = [vp, vp, ctypes.c_int64, vp]
     lib.vdp_cvt_bf16.argtypes = [vp, vp, ctypes.c_int64, vp]
     lib.vdp_row_swap.argtypes = [vp, vp, vp, vp]
     lib.vdp_claims.argtypes = [vp, vp, ctypes.c_int, ctypes.c_int, vp]
-    for f in (lib.vdp_mfma_bf16, lib.vdp_exp2, lib.vdp_cvt_bf16, lib.vdp_row_swap, lib.vdp_claims):
+    for f in (lib.vdp_mfma_bf16, lib.vdp_mfma32_bf16, lib.vdp_exp2, lib.vdp_cvt_bf16, lib.vdp_row_swap, lib.vdp_claims):
         f.restype = ctypes.c_int
     return lib
 
@@ -205,6 +209,55 @@ def test_mfma_zero_b_returns_the_accumulator(probes):
         U.say("  mfma with B = %s: %d of %d accumulators changed (%d denormal, %d -0 -> +0)"
               % ("+0" if zero == 0 else "-0", bad, d.size, den, int(np.sum(u == 0x80000000))))
         assert bad == 0
+
+
+def run_mfma32(lib, a_bits, b_bits, c):
+    """The same dot products as two chained 32 x 32 x 16 steps: a_bits and
+    b_bits [T, 32, 32], c [T, 32, 32]."""
+    t = a_bits.shape[0]
+    da = torch.from_numpy(np.ascontiguousarray(a_bits).view(np.int16)).cuda()
+    db = torch.from_numpy(np.ascontiguousarray(b_bits).view(np.int16)).cuda()
+    dc = torch.from_numpy(np.ascontiguousarray(c, dtype=np.float32)).cuda()
+    dd = torch.full((t, 32, 32), float("nan"), dtype=torch.float32, device="cuda")
+    assert lib.vdp_mfma32_bf16(da.data_ptr(), db.data_ptr(), dc.data_ptr(), dd.data_ptr(), t, _stream()) == 0
+    torch.cuda.synchronize()
+    return dd.cpu().numpy()
+
+
+@pytest.mark.parametrize("kind", ["normal", "wide", "tiny", "weights", "special"])
+def test_mfma_32x32x16_pair_equals_16x16x32(probes, kind):
+    """262,144 cells of each kind: N(0, 1); magnitudes over 2^+-24 in a row (the
+    order and the alignment of the internal sums show); products and
+    accumulators in the denormal range; softmax weights (many of them zero)
+    with a non-negative accumulator; infinities and NaN among the operands
+    (a NaN result's payload aside)."""
+    rng = W.rng_for(40, 11)
+    t = 256
+    a, b = W.normal_bf16(rng, (t, 32, 32)), W.normal_bf16(rng, (t, 32, 32))
+    c = rng.standard_normal((t, 32, 32)).astype(np.float32) * 4
+    if kind == "wide":
+        f = W.bf16_to_f32(a) * np.exp2(rng.integers(-24, 25, a.shape)).astype(np.float32)
+        a = W.bf16_bits(f)
+    elif kind == "tiny":
+        a = W.bf16_bits(W.bf16_to_f32(a) * np.float32(2.0**-70))
+        b = W.bf16_bits(W.bf16_to_f32(b) * np.float32(2.0**-62))
+        c = (c * np.float32(2.0**-130)).astype(np.float32)
+    elif kind == "weights":
+        w = np.exp2(-rng.exponential(8.0, b.shape)) * (rng.random(b.shape) < 0.7)
+        b, c = W.bf16_bits(w.astype(np.float32)), np.abs(c)
+    elif kind == "special":
+        a[rng.random(a.shape) < 0.002] = 0x7F80
+        a[rng.random(a.shape) < 0.001] = W.BF16_QNAN
+        b[rng.random(b.shape) < 0.002] = 0xFF80
+    d32 = run_mfma32(probes, a, b, c)
+    for x in range(2):
+        for y in range(2):
+            sx, sy = slice(16 * x, 16 * x + 16), slice(16 * y, 16 * y + 16)
+            d16 = run_mfma(probes, a[:, sx], b[:, :, sy], c[:, sx, sy])
+            got = d32[:, sx, sy]
+            nan = np.isnan(d16)
+            assert np.array_equal(nan, np.isnan(got))
+            assert np.array_equal(bits32(d16)[~nan], bits32(got)[~nan]), (kind, x, y)
 
 
 def test_exp2_special_values(probes):
