@@ -222,16 +222,18 @@ __device__ __forceinline__ void store_row(const Params& P, const f32x4 (&u)[D / 
   }
 }
 
-// The same from the accumulators of a 32-column block: d = 32 m + 8 (i / 4) + 4 hf + i % 4.
-template <int D>
-__device__ __forceinline__ void store_row32(const Params& P, const f32x16 (&u)[D / 32], float M,
-                                            float Z, int64_t tok, int head) {
+// The same from the accumulators of a 32-column block, NM 32-d blocks from
+// block m0: d = 32 (m0 + m) + 8 (i / 4) + 4 hf + i % 4.  The log-sum-exp goes with
+// block 0.
+template <int D, int NM>
+__device__ __forceinline__ void store_row32(const Params& P, const f32x16 (&u)[NM], float M, float Z,
+                                            int64_t tok, int head, int m0 = 0) {
   const int hf = __lane_id() >> 5;
   const float rho = final_scale(Z);
-  if (P.lse && hf == 0) P.lse[tok * P.hq + head] = final_lse(M, Z);
-  uint16_t* o = P.out + (tok * P.hq + head) * D + 4 * hf;
+  if (P.lse && hf == 0 && m0 == 0) P.lse[tok * P.hq + head] = final_lse(M, Z);
+  uint16_t* o = P.out + (tok * P.hq + head) * D + 32 * m0 + 4 * hf;
 #pragma unroll
-  for (int m = 0; m < D / 32; ++m)
+  for (int m = 0; m < NM; ++m)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       u16x4 v;
@@ -1278,7 +1280,7 @@ __device__ __forceinline__ bool inwave_split_item(const Params& P, int vb, Split
 // blocks of a die are dispatched in that order, which keeps the longest
 // items off the end of the launch.  Which workgroup computes a row never
 // changes its bits.
-__device__ __forceinline__ bool inwave_chunk_item(const Params& P, int& g, int& r, int& qt,
+__device__ __forceinline__ bool inwave_chunk_item(const Params& P, int cols, int& g, int& r, int& qt,
                                                   Req& R) {
   constexpr int C = kInWaveChunks;
   const int lane = __lane_id();
@@ -1300,7 +1302,7 @@ __device__ __forceinline__ bool inwave_chunk_item(const Params& P, int& g, int& 
     if (64 * c + lane < P.num_seqs) {
       const Req Rl = make_req(P, cq0[c], cq1[c], cn[c]);
       const int ncols = Rl.s * P.G;
-      if (Rl.valid && ncols > P.split_cols) cnt[c] = (ncols + kChunkCols - 1) / kChunkCols;
+      if (Rl.valid && ncols > P.split_cols) cnt[c] = (ncols + cols - 1) / cols;
     }
     incl[c] = wave_scan_dpp(cnt[c]);
     per_head += __builtin_amdgcn_readlane(incl[c], 63);
@@ -1370,7 +1372,7 @@ __device__ __forceinline__ bool inwave_chunk_item(const Params& P, int& g, int& 
   R = make_req(P, q0, q1, n);
   const int ncols = R.s * P.G;
   return r < P.num_seqs && g < P.hkv && R.valid && ncols > P.split_cols &&
-         qt < (ncols + kChunkCols - 1) / kChunkCols;
+         qt < (ncols + cols - 1) / cols;
 }
 
 // The new tokens of the chunk-path requests, written by the split launch's
@@ -1832,6 +1834,9 @@ __device__ __forceinline__ void order_pv_reads() {
 #define VD_CHUNK_STAGES 2
 #endif
 constexpr int kChunkStages = VD_CHUNK_STAGES;
+// The paired chunk kernel: wavefronts per group, query-head rows per workgroup.
+constexpr int kPairWaves = 2;
+constexpr int kPairCols = 32 * kPairWaves;
 
 // Entries lp0 .. lp0 + NE - 1 of a page-table row into spid (every thread of
 // a 256-thread workgroup takes part; the caller synchronises): the page id,
@@ -1854,6 +1859,132 @@ __device__ __forceinline__ void load_pid_window(const Params& P, const int32_t* 
   }
 }
 
+// The copies of one tile by QW wavefronts (those of wave 0 .. QW - 1): each
+// moves NP whole page blocks of the tile's 4 K and 4 V blocks, from block blk0
+// (the SUBS 1 KB parts of a block share one M0 setting).  In LDS the two
+// 128-byte runs {slots 0-3, 4-7} and {8-11, 12-15} of every odd group of 16 d of a V
+// block change places, so that the 32 lanes of half a V operand read touch
+// distinct banks.
+//
+// The page ids of a tile's copies are read one tile ahead (load_ids: scalar
+// loads that return during the wait for the copies in flight), from entries
+// clamped to the request's pages.  Read where they were used, four dependent
+// loads a tile held up the copies: 806 against 723 us for a 512-token chunk at
+// key 30000 (one request), 499 against 476 us for the 8B mixed batch.
+template <int D, int QW>
+struct TileCopies {
+  static constexpr int BLK = kPage * D;
+  static constexpr int kCopies = 2 * kPagesPerTile * BLK / (QW * 512);  // 1 KB each, per wavefront
+  static constexpr int SUBS = BLK / 512;
+  static constexpr int NP = kCopies / SUBS;
+  static_assert(kCopies % SUBS == 0 && kPagesPerTile % NP == 0, "whole page blocks per wavefront");
+  const int32_t* ptrow;
+  const uint16_t* pool;
+  int64_t page_elems;
+  int npages, num_pages, blk0;
+  int ids[NP];
+
+  __device__ __forceinline__ TileCopies(const Params& P, const int32_t* row, int pages, int g,
+                                        int wave, int lane)
+      : ptrow(row), page_elems((int64_t)P.hkv * BLK), npages(pages), num_pages(P.num_pages),
+        blk0(wave * NP) {
+    const bool v = blk0 >= kPagesPerTile;
+    pool = (v ? P.vpool : P.kpool) + (int64_t)g * BLK + 8 * (v ? lane ^ ((lane >> 5) << 3) : lane);
+  }
+  __device__ __forceinline__ void load_ids(int kt) {
+    typedef __attribute__((address_space(4))) const int32_t const_i32;
+#pragma unroll
+    for (int i = 0; i < NP; ++i)
+      ids[i] = ((const const_i32*)ptrow)[min(kt * kPagesPerTile + blk0 % kPagesPerTile + i, npages - 1)];
+  }
+  // block i of the wavefront's share
+  __device__ __forceinline__ void fetch_block(uint16_t* tile, int i) const {
+    const int page = (unsigned)ids[i] < (unsigned)num_pages ? ids[i] : 0;
+    const uint32_t dst = (uint32_t)(uintptr_t)(tile + (blk0 + i) * BLK);
+    lds_dma16_run<SUBS>(pool + page * page_elems, uni((int)dst));
+  }
+  __device__ __forceinline__ void fetch(uint16_t* tile) const {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) fetch_block(tile, i);
+  }
+};
+
+// Zeroes, in a staged tile kt, the K rows and V entries of keys >= n or of
+// invalid pages (a request's last, ragged tile only); threads tid of nthreads.
+template <int D>
+__device__ __forceinline__ void mask_tile(const Params& P, const int32_t* ptrow, const Req& R, int g,
+                                          int kt, uint16_t* tile, int tid, int nthreads) {
+  constexpr int BLK = kPage * D;
+  constexpr int TILE = 2 * kPagesPerTile * BLK;
+  const int j0 = kt * kTileKeys;
+  bool pvalid[kPagesPerTile];
+#pragma unroll
+  for (int b = 0; b < kPagesPerTile; ++b)
+    pvalid[b] = page_block(P, ptrow, kt * kPagesPerTile + b, R.n, g) >= 0;
+  for (int ch = tid; ch < TILE / 8; ch += nthreads) {
+    const int blk = ch / (BLK / 8), off = (ch % (BLK / 8)) * 8;
+    const int b = blk % kPagesPerTile;
+    const int kbase = j0 + 16 * b;
+    const bool pok = pvalid[b];
+    u16x8* p = reinterpret_cast<u16x8*>(tile + blk * BLK + off);
+    u16x8 v = *p;
+    if (blk < kPagesPerTile) {
+      const int slot = (off / 8) % 16;  // K block: [D/8][16][8]
+      if (!pok || kbase + slot >= R.n) v = zero8();
+    } else {
+      const int sg = ((off / 64) % 4) ^ ((off / 256) & 1);  // V block: [D/16][4][16][4], runs as above
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = (pok && kbase + 4 * sg + (e % 4) < R.n) ? v[e] : (uint16_t)0;
+    }
+    *p = v;
+  }
+}
+
+// One wavefront's tile in the paired chunk kernel: Q.K, softmax and P.V of its
+// 32 columns over the staged tile T (first key j0); between(part) runs before
+// Q.K (0), before (1) and after (2) the softmax.
+template <int D, bool WIN, class Between>
+__device__ __forceinline__ void chunk_tile(const uint16_t* T, const u16x8 (&qf)[D / 16],
+                                           State32<D>& st, int j0, int pos, int lo, float c,
+                                           const Between& between) {
+  constexpr int BLK = kPage * D;
+  const int lane = __lane_id(), col = lane & 31, hf = lane >> 5;
+  f32x16 acc[2];
+  between(0);
+  // The two wavefronts of a SIMD belong to different workgroups; the one
+  // issuing matrix-core work gets the higher issue priority, the other's
+  // softmax fills the vector ALU around it.
+  __builtin_amdgcn_s_setprio(2);
+  // key 32 b + col: page 2 b + col / 16, slot col % 16
+  const uint16_t* TK = T + (col / 16) * BLK + 128 * hf + 8 * (col % 16);
+  tile_scores32<D>(
+      [&](int b, int ks) { return *reinterpret_cast<const u16x8*>(TK + 2 * b * BLK + 256 * ks); },
+      qf, acc);
+  order_qk_reads<D>();
+  between(1);
+  __builtin_amdgcn_s_setprio(0);
+  // every key of the tile visible to every column
+  const bool open = __all(pos >= j0 + kTileKeys - 1 && lo <= j0);
+  TileWeights32 w;
+  if (open)
+    w = tile_softmax32<false, WIN>(st.m, st.z, acc, j0, pos, lo, c);
+  else
+    w = tile_softmax32<true, WIN>(st.m, st.z, acc, j0, pos, lo, c);
+  between(2);
+  __builtin_amdgcn_s_setprio(2);
+  // d 32 m + col, slots 4 (hf + 2 y) .. + 3 of the pages 2 b and 2 b + 1
+  const uint16_t* TV = T + kPagesPerTile * BLK + 256 * (col / 16) + 64 * (hf ^ (col / 16)) + 4 * (col % 16);
+#pragma unroll
+  for (int m = 0; m < D / 32; ++m)
+    tile_pv_block32<D>(st, w, m, [&](int x) {
+      const uint16_t* v = TV + 2 * (x / 2) * BLK + 128 * (x % 2) + 512 * m;
+      return cat4(lds_read8<u16x4>(v), lds_read8<u16x4>(v + BLK));
+    });
+  order_pv_reads<D>();
+  tile_commit32<D>(st, w);
+  __builtin_amdgcn_s_setprio(0);
+}
+
 // Two workgroups per CU (waves_per_eu 2: at most 256 registers per lane, and
 // two LDS rings of kChunkStages tiles): while one wavefront of a SIMD waits on
 // its softmax chain, the other issues matrix-core work.  WIN: the handle has a
@@ -1864,7 +1995,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   constexpr int BLK = kPage * D;                   // elements of one page block
   constexpr int NBLK = 2 * kPagesPerTile;          // 4 K blocks then 4 V blocks
   constexpr int TILE = NBLK * BLK;                 // elements of one staged tile
-  constexpr int WCH = TILE / (4 * 512);            // 1 KB copies per wavefront per tile
   constexpr int STAGES = kChunkStages;
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];  // [STAGES][NBLK][BLK]
   const int wave = uni(threadIdx.x >> 6);
@@ -1879,7 +2009,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   int g, r, qt;
   Req R;
   if (P.inwave) {
-    if (!inwave_chunk_item(P, g, r, qt, R)) return;
+    if (!inwave_chunk_item(P, kChunkCols, g, r, qt, R)) return;
   } else {
     const int per_head = P.off_chunk[P.num_seqs];
     const int total = per_head * P.hkv;
@@ -1932,65 +2062,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     bad = bad || pg < 0 || pg >= P.num_pages;
   }
   const bool pages_ok = !__any(bad);
-  // This wavefront's WCH direct loads of a tile: NP whole page blocks of its 4
-  // K and 4 V blocks, from block blk0 (SUBS 1 KB parts of a block share one M0
-  // setting).  In LDS the two 128-byte runs {slots 0-3, 4-7} and {8-11, 12-15}
-  // of every odd group of 16 d of a V block change places, so that the 32
-  // lanes of half a V operand read touch distinct banks.
-  constexpr int SUBS = BLK / 512;
-  constexpr int NP = WCH / SUBS;
-  static_assert(WCH % SUBS == 0 && kPagesPerTile % NP == 0, "whole page blocks per wavefront");
-  const int blk0 = wave * NP;
-  const bool copies_v = blk0 >= kPagesPerTile;
-  const uint16_t* pool = (copies_v ? P.vpool : P.kpool) + (int64_t)g * BLK +
-                         8 * (copies_v ? lane ^ ((lane >> 5) << 3) : lane);
-  const int64_t page_elems = (int64_t)P.hkv * BLK;
-  // The page ids of a tile's copies are read one tile ahead (scalar loads that
-  // return during the wait for the copies in flight), from entries clamped to
-  // the request's pages.  Read where they were used, four dependent loads a
-  // tile held up the copies: 806 against 723 us for a 512-token chunk at key
-  // 30000 (one request), 499 against 476 us for the 8B mixed batch.
-  int ids[NP];
-  auto load_ids = [&](int kt) {
-    typedef __attribute__((address_space(4))) const int32_t const_i32;
-#pragma unroll
-    for (int i = 0; i < NP; ++i)
-      ids[i] = ((const const_i32*)ptrow)[min(kt * kPagesPerTile + blk0 % kPagesPerTile + i, npages - 1)];
-  };
-  auto fetch = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < NP; ++i) {
-      const int page = (unsigned)ids[i] < (unsigned)P.num_pages ? ids[i] : 0;
-      const uint32_t dst = (uint32_t)(uintptr_t)(lds + (buf * NBLK + blk0 + i) * BLK);
-      lds_dma16_run<SUBS>(pool + page * page_elems, uni((int)dst));
-    }
-  };
-  // Zeroes, in stage buf, the K rows and V entries of keys >= n or of
-  // invalid pages (a request's last, ragged tile only).
-  auto mask_stage = [&](int kt, int buf) {
-    const int j0 = kt * kTileKeys;
-    bool pvalid[kPagesPerTile];
-#pragma unroll
-    for (int b = 0; b < kPagesPerTile; ++b)
-      pvalid[b] = page_block(P, ptrow, kt * kPagesPerTile + b, R.n, g) >= 0;
-    for (int ch = threadIdx.x; ch < TILE / 8; ch += 256) {
-      const int blk = ch / (BLK / 8), off = (ch % (BLK / 8)) * 8;
-      const int b = blk % kPagesPerTile;
-      const int kbase = j0 + 16 * b;
-      const bool pok = pvalid[b];
-      u16x8* p = reinterpret_cast<u16x8*>(lds + (buf * NBLK + blk) * BLK + off);
-      u16x8 v = *p;
-      if (blk < kPagesPerTile) {
-        const int slot = (off / 8) % 16;  // K block: [D/8][16][8]
-        if (!pok || kbase + slot >= R.n) v = zero8();
-      } else {
-        const int sg = (off / 64) % 4 ^ ((off / 256) & 1);  // V block: [D/16][4][16][4], runs as above
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = (pok && kbase + 4 * sg + (e % 4) < R.n) ? v[e] : (uint16_t)0;
-      }
-      *p = v;
-    }
-  };
+  TileCopies<D, 4> copies(P, ptrow, npages, g, wave, lane);
   auto tile_is_full = [&](int kt) {
     if ((kt + 1) * kTileKeys > R.n) return false;
     if (pages_ok) return true;
@@ -2004,10 +2076,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
   for (int t = 0; t < STAGES - 1; ++t)
     if (kt_first + t < ntiles) {
-      load_ids(kt_first + t);
-      fetch((kt_first + t) % STAGES);
+      copies.load_ids(kt_first + t);
+      copies.fetch(lds + (kt_first + t) % STAGES * TILE);
     }
-  load_ids(kt_first + STAGES - 1);
+  copies.load_ids(kt_first + STAGES - 1);
   for (int kt = kt_first; kt < ntiles; ++kt) {
     const int j0 = kt * kTileKeys;
     const int k = kt / kTilesPerSplit;
@@ -2016,22 +2088,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int later = min(STAGES - 2, ntiles - 1 - kt);
     static_assert(STAGES >= 2 && STAGES <= 5, "ring depth");
     if (later >= 3)
-      wait_vmcnt<3 * WCH>();
+      wait_vmcnt<3 * TileCopies<D, 4>::kCopies>();
     else if (later == 2)
-      wait_vmcnt<2 * WCH>();
+      wait_vmcnt<2 * TileCopies<D, 4>::kCopies>();
     else if (later == 1)
-      wait_vmcnt<WCH>();
+      wait_vmcnt<TileCopies<D, 4>::kCopies>();
     else
       wait_vmcnt<0>();
     lds_barrier();  // every wavefront's part of tile kt is in LDS; tile kt - 1 is consumed
     if (!tile_is_full(kt)) {
-      mask_stage(kt, buf);
+      mask_tile<D>(P, ptrow, R, g, kt, lds + buf * TILE, threadIdx.x, 256);
       lds_barrier();
     }
-    if (kt + STAGES - 1 < ntiles) fetch((kt + STAGES - 1) % STAGES);
+    if (kt + STAGES - 1 < ntiles) copies.fetch(lds + (kt + STAGES - 1) % STAGES * TILE);
     if (kt % kTilesPerSplit == 0 || kt == kt_first) state32_init(st);
-    const uint16_t* T = lds + buf * NBLK * BLK;
+    const uint16_t* T = lds + buf * TILE;
     if (wave_pmax >= j0 && j0 + kTileKeys - 1 >= wave_lo) {
+      // (as a call of chunk_tile the compiler spills 98 registers in this kernel)
       f32x16 acc[2];
       // The two wavefronts of a SIMD belong to different workgroups; the one
       // issuing matrix-core work gets the higher issue priority, the other's
@@ -2064,7 +2137,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       tile_commit32<D>(st, w);
       __builtin_amdgcn_s_setprio(0);
     }
-    load_ids(kt + STAGES);
+    copies.load_ids(kt + STAGES);
     if (kt % kTilesPerSplit == kTilesPerSplit - 1 || kt == ntiles - 1) {
       // split k ends: fold it into the running merge for columns that have it
       // (a column's splits run from the one holding its window start)
@@ -2087,7 +2160,189 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
     }
   }
-  if (live) store_row32<D>(P, W, M, Z, R.q0 + c / P.G, g * P.G + c % P.G);
+  if (live) store_row32<D, D / 32>(P, W, M, Z, R.q0 + c / P.G, g * P.G + c % P.G);
+}
+
+// ---------------------------------------------------------------------------
+// paired chunk kernel: the chunk kernel's work for calls whose items would
+// leave CUs idle (run_chunks has the rule).  Two groups of two wavefronts per
+// workgroup run the same 64 query-head rows over alternate splits, each group
+// with its own LDS ring, one workgroup barrier per tile.  After each pair of
+// splits the groups exchange their states through LDS -- group 0 folds the
+// lower half of d, group 1 the upper -- so every column still folds its splits in
+// ascending order, with the same operations.  Bound by the latency of a tile at
+// one wavefront per SIMD.  A wavefront's copies of the next tile are issued in
+// three parts (before Q.K, before and after the softmax): the vector memory
+// pipe takes 64 bytes a cycle per CU, and issued at once they held up the
+// wavefront.  A 512-token chunk at key 30000 (one request, 8 KV heads, 128
+// items of the chunk kernel on 256 CUs): the chunk kernel 670 us; this 488 with
+// the copies issued at once, 440 in parts; with groups of four wavefronts
+// (128 rows per workgroup) 522.
+// ---------------------------------------------------------------------------
+template <int D, bool WIN>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void chunk_pair_kernel(Params P) {
+  constexpr int QW = kPairWaves;
+  constexpr int TILE = 2 * kPagesPerTile * kPage * D;
+  constexpr int COLS = kPairCols;
+  constexpr int H = D / 64;  // 32-d blocks of a half
+  // [2 groups][2 stages][TILE], then the (m, z) of both groups' columns
+  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
+  float2* mz = reinterpret_cast<float2*>(lds + 4 * TILE);  // [2][COLS]
+  const int wave = uni(threadIdx.x >> 6);
+  const int gi = wave / QW, wq = wave % QW;
+  const int lane = __lane_id();
+  const int col = lane & 31;
+  const int window = WIN ? P.window : 0;
+  int g, r, qt;
+  Req R;
+  if (!inwave_chunk_item(P, COLS, g, r, qt, R)) return;
+  const int ncols = R.s * P.G;
+  const int c0 = qt * COLS;
+  const int cend = min(ncols, c0 + COLS);
+  const int pmax = R.n - R.s + (cend - 1) / P.G;  // last position of the block
+  const int c = c0 + wq * 32 + col;
+  const bool live = c < cend;
+  const int pos = live ? R.n - R.s + c / P.G : -1;
+  const int lo = window_lo(pos, window);
+  u16x8 qf[D / 16];
+  load_q32<D>(P, qf, R.q0 + (live ? c / P.G : 0), g * P.G + (live ? c % P.G : 0), live);
+  const int wave_c1 = min(cend, c0 + wq * 32 + 32) - 1;
+  const int wave_pmax = wave_c1 >= c0 + wq * 32 ? R.n - R.s + wave_c1 / P.G : -1;
+  const int wave_lo = window_lo(R.n - R.s + min(c0 + wq * 32, cend - 1) / P.G, window);
+
+  const int32_t* ptrow = P.pt + (int64_t)r * P.pt_stride;
+  const int ntiles = pmax / kTileKeys + 1;
+  const int kt_first = window_lo(R.n - R.s + c0 / P.G, window) / kTileKeys;
+  const int npages = (R.n + kPage - 1) / kPage;
+  bool bad = false;
+  for (int e = lane; e < npages; e += 64) {
+    const int32_t pg = ptrow[e];
+    bad = bad || pg < 0 || pg >= P.num_pages;
+  }
+  const bool pages_ok = !__any(bad);
+  auto tile_is_full = [&](int kt) {
+    if ((kt + 1) * kTileKeys > R.n) return false;
+    if (pages_ok) return true;
+#pragma unroll
+    for (int b = 0; b < kPagesPerTile; ++b)
+      if (page_block(P, ptrow, kt * kPagesPerTile + b, R.n, g) < 0) return false;
+    return true;
+  };
+  // Rounds of two splits ks, ks + 1 (group gi runs ks + gi), each of up to 16
+  // steps: step i is tile 16 (ks + gi) + i, when the item has that tile.
+  const int ks0 = kt_first / kTilesPerSplit, ks1 = (ntiles - 1) / kTilesPerSplit;
+  auto has_tile = [&](int kt) { return kt >= kt_first && kt < ntiles; };
+  auto first_step = [&](int ks) { return ks == ks0 && ks == ks1 ? kt_first % kTilesPerSplit : 0; };
+  auto end_step = [&](int ks) { return ks == ks1 ? (ntiles - 1) % kTilesPerSplit + 1 : kTilesPerSplit; };
+
+  TileCopies<D, QW> copies(P, ptrow, npages, g, wq, lane);
+  uint16_t* ring = lds + gi * 2 * TILE;
+  State32<D> st;
+  float M = 0.f, Z = 0.f;
+  f32x16 W[H];
+#pragma unroll
+  for (int m = 0; m < H; ++m) W[m] = f32x16{};
+
+  wait_vmcnt<0>();  // the Q operands are in registers before any tile copy is issued
+  int buf = 0;
+  int nks = ks0, ni = first_step(ks0);  // the step whose copies are issued next
+  auto advance = [&]() {
+    if (++ni == end_step(nks)) {
+      nks += 2;
+      ni = first_step(nks);
+    }
+    copies.load_ids((nks + gi) * kTilesPerSplit + ni);
+  };
+  auto has_next = [&]() { return nks <= ks1 && has_tile((nks + gi) * kTilesPerSplit + ni); };
+  copies.load_ids((nks + gi) * kTilesPerSplit + ni);
+  if (has_next()) copies.fetch(ring);
+  advance();
+  for (int ks = ks0; ks <= ks1; ks += 2) {
+    state32_init(st);
+    const int i1 = end_step(ks);
+    for (int i = first_step(ks); i < i1; ++i) {
+      const int kt = (ks + gi) * kTilesPerSplit + i;
+      const int j0 = kt * kTileKeys;
+      wait_vmcnt<0>();  // this wavefront's copies of the step have landed
+      lds_barrier();    // ... and every wavefront's; the step before is consumed
+      const int ka = ks * kTilesPerSplit + i, kb = ka + kTilesPerSplit;
+      if ((has_tile(ka) && !tile_is_full(ka)) || (has_tile(kb) && !tile_is_full(kb))) {
+        if (has_tile(kt) && !tile_is_full(kt))
+          mask_tile<D>(P, ptrow, R, g, kt, ring + buf * TILE, wq * 64 + lane, 64 * QW);
+        lds_barrier();
+      }
+      const bool more = has_next();
+      auto between = [&](int part) {
+        constexpr int NP = TileCopies<D, QW>::NP;
+#pragma unroll
+        for (int i = 0; i < NP; ++i)
+          if (more && part == 3 * i / NP) copies.fetch_block(ring + (buf ^ 1) * TILE, i);
+      };
+      if (has_tile(kt) && wave_pmax >= j0 && j0 + kTileKeys - 1 >= wave_lo) {
+        chunk_tile<D, WIN>(ring + buf * TILE, qf, st, j0, pos, lo, P.c, between);
+      } else {
+#pragma unroll
+        for (int part = 0; part < 3; ++part) between(part);
+      }
+      advance();
+      buf ^= 1;
+    }
+    // exchange: each group leaves the other's half of its U in its own stage
+    // just consumed
+    lds_barrier();
+    f32x4* mine = reinterpret_cast<f32x4*>(ring + (buf ^ 1) * TILE) + wq * (4 * H * 64) + lane;
+    const f32x4* theirs =
+        reinterpret_cast<const f32x4*>(lds + (gi ^ 1) * 2 * TILE + (buf ^ 1) * TILE) +
+        wq * (4 * H * 64) + lane;
+    if (lane < 32) mz[gi * COLS + wq * 32 + lane] = float2{st.m, st.z};
+    auto give = [&](int m0) {
+#pragma unroll
+      for (int m = 0; m < H; ++m)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          mine[(4 * m + q) * 64] = f32x4{st.u[m0 + m][4 * q], st.u[m0 + m][4 * q + 1],
+                                         st.u[m0 + m][4 * q + 2], st.u[m0 + m][4 * q + 3]};
+    };
+    if (gi == 0) give(H); else give(0);
+    lds_barrier();
+    f32x16 other[H];
+#pragma unroll
+    for (int m = 0; m < H; ++m)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f32x4 v = theirs[(4 * m + q) * 64];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) other[m][4 * q + e] = v[e];
+      }
+    // split k of the column folded into (M, Z, W), as in the chunk kernel
+    auto fold = [&](int k, int from, auto u) {
+      const int klo = lo / kSplitKeys;
+      if (pos < 0 || k > pos / kSplitKeys || k < klo) return;
+      const float2 s = mz[from * COLS + wq * 32 + col];
+      if (k == klo) {
+        M = s.x;
+        Z = s.y;
+#pragma unroll
+        for (int m = 0; m < H; ++m) W[m] = u(m);
+      } else {
+        const FoldScalars f = fold_scalars(M, Z, s.x, s.y);
+#pragma unroll
+        for (int m = 0; m < H; ++m)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) W[m][e] = fold_value(W[m][e], u(m)[e], f);
+        M = f.M;
+        Z = f.Z;
+      }
+    };
+    if (gi == 0) {
+      fold(ks, 0, [&](int m) { return st.u[m]; });
+      fold(ks + 1, 1, [&](int m) { return other[m]; });
+    } else {
+      fold(ks, 0, [&](int m) { return other[m]; });
+      fold(ks + 1, 1, [&](int m) { return st.u[H + m]; });
+    }
+  }
+  if (live) store_row32<D, H>(P, W, M, Z, R.q0 + c / P.G, g * P.G + c % P.G, gi * H);
 }
 
 // Dynamic LDS bytes of the chunk kernel: kChunkStages stages of 8 page blocks.
@@ -2096,8 +2351,15 @@ constexpr size_t chunk_lds_bytes() {
   return (size_t)kChunkStages * 2 * kPagesPerTile * kPage * D * sizeof(uint16_t);
 }
 
-// ... and of the shared-prefix kernel: the same ring, then the page ids of an
-// item's split.
+// ... of the paired chunk kernel: a 2-stage ring per group, then (m, z) of both
+// groups' columns.
+template <int D>
+constexpr size_t chunk_pair_lds_bytes() {
+  return (size_t)4 * 2 * kPagesPerTile * kPage * D * sizeof(uint16_t) + 2 * kPairCols * sizeof(float2);
+}
+
+// ... and of the shared-prefix kernel: the chunk kernel's ring, then the page
+// ids of an item's split.
 template <int D>
 constexpr size_t prefix_lds_bytes() {
   return chunk_lds_bytes<D>() + (size_t)(kSplitKeys / kPage) * sizeof(int32_t);
@@ -2757,11 +3019,31 @@ int run_merge(const Params& P, hipStream_t s) {
 
 template <int D>
 int run_chunks(const Params& P, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr) {
-  // upper bound of sum_r Hkv * ceil(s_r G / 128) <= Hkv (ceil(T G / 128) + B),
-  // rounded up to a multiple of the dies
-  int64_t blocks = (int64_t)P.hkv * ((P.T * P.G + kChunkCols - 1) / kChunkCols + P.num_seqs);
-  blocks = (blocks + P.xcds - 1) / P.xcds * P.xcds;
+  // upper bound of the items, Hkv sum_r ceil(s_r G / cols) <= Hkv floor((T G +
+  // B (cols - 1)) / cols)
+  auto items = [&](int cols) {
+    return (int64_t)P.hkv * ((P.T * P.G + (int64_t)P.num_seqs * (cols - 1)) / cols);
+  };
+  auto grid = [&](int64_t n) { return (n + P.xcds - 1) / P.xcds * P.xcds; };
+  const int64_t blocks = grid(items(kChunkCols));
   if (blocks > INT32_MAX) return VD_ERR_INVALID_ARG;
+  // Paired items when every one of them finds a CU of its own and some context
+  // is longer than a split: the chunk kernel then has at most half a
+  // workgroup per CU, and runs a row's splits one after the other.  With more
+  // items a second round of pairs takes as long as the chunk kernel, which
+  // runs two workgroups on a CU (calls, us, chunk kernel against pairs: a
+  // 1000-token chunk at key 30000, 252 items of the chunk kernel, 748 / 910; 512
+  // tokens, 128 items, 671 / 438; 64 tokens at key 8000, 16 items, 190 / 121).
+  if (P.inwave && P.max_splits > 1 && items(kPairCols) <= device_geometry().cus) {
+    constexpr size_t lds = chunk_pair_lds_bytes<D>();
+    const auto kern = P.window > 0 ? &chunk_pair_kernel<D, true> : &chunk_pair_kernel<D, false>;
+    static std::atomic<unsigned char> lds_set[2][kMaxDevices];
+    if (set_lds_limit(reinterpret_cast<const void*>(kern), (int)lds, lds_set[P.window > 0]) != hipSuccess)
+      return VD_ERR_LAUNCH;
+    hipExtLaunchKernelGGL(kern, dim3((unsigned)grid(items(kPairCols))), dim3(128 * kPairWaves),
+                          (uint32_t)lds, s, e0, e1, 0, P);
+    return launched();
+  }
   constexpr size_t lds = chunk_lds_bytes<D>();
   // a handle's window is fixed at creation: one kernel per handle
   const auto kern = P.window > 0 ? &chunk_kernel<D, true> : &chunk_kernel<D, false>;

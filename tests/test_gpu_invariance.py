@@ -265,3 +265,39 @@ def test_full_size_decode_probe_batch_1_17_64():
     solo = outs(W.config2(batch=1, probe_slot=0))
     for batch, slot in [(17, 9), (64, 33)]:
         U.assert_same_bits(solo, outs(W.config2(batch=batch, probe_slot=slot, perm_stream=5)))
+
+
+PAIR_SHAPES = [W.LLAMA8B, W.Shape(14, 2, 64), W.Shape(32, 8, 128, window=1500)]
+
+
+@pytest.mark.parametrize("shape", PAIR_SHAPES, ids=["d128-g4", "d64-g7", "d128-window"])
+@pytest.mark.parametrize("n,s", [
+    (1025, 33),    # a second split of one key
+    (2048, 65),    # two whole splits
+    (2049, 128),   # a third of one key, alone in its round
+    (3100, 17),    # rows in one split, an odd count of splits
+    (4097, 90),    # rows on both sides of a split edge
+    (5000, 257),
+])
+def test_paired_chunks_equal_chunks(shape, n, s):
+    """A prefill chunk alone (few items: the paired chunk kernel, where its
+    context is longer than a split) equals, bit for bit and in its log-sum-exp,
+    the same chunk in a call with enough other rows for the chunk kernel; and
+    sampled rows match the oracle."""
+    p = W.make_prompt(shape, n, 71, n, q_window=s)
+    other = W.make_prompt(shape, 1200 * 32 // shape.num_q_heads, 71, 1)
+    rng = W.rng_for(71, 4)
+    alone = W.place(shape, [p], [W.Req(0, n, s)], rng)
+    both = W.place(shape, [other, p], [W.Req(0, other.length, other.length), W.Req(1, n, s)], rng)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+
+    def items(call):  # an upper bound, 64 query-head rows each
+        rows = call.total_q_tokens * shape.group + 63 * call.num_seqs
+        return shape.num_kv_heads * (rows // 64)
+
+    assert items(alone) <= cus < items(both)
+    a, la = U.gpu_run(alone, with_lse=True)
+    b, lb = U.gpu_run(both, with_lse=True)
+    assert np.array_equal(a, b[other.length:]) and np.array_equal(la, lb[other.length:])
+    U.assert_written(U.by_position(alone, a))
+    U.parity(alone, a, rows=[0, s // 2, s - 1])
