@@ -212,11 +212,17 @@ int vd_attn_forward_noalloc(const vd_attn* h, const vd_attn_batch* batch, void* 
  *           split writes its output rows directly; otherwise each item writes
  *           a partial state;
  *   chunks: rows of requests with s_r * (Hq / Hkv) > 32 -- one work item per
- *           (request, KV head, 128 query-head rows); folds the splits in
+ *           (request, KV head, 128 query-head rows), or per 64 rows when those
+ *           number at most one per compute unit; folds the splits in
  *           registers and writes their output rows;
  *   merge:  folds the partial states of the split-phase rows of requests
  *           with more than one split, in ascending split order, and writes
- *           their output rows. */
+ *           their output rows; launches nothing when max_context_len is at
+ *           most one split (1024).
+ * When total_q_tokens and max_q_len leave every request more rows than the
+ * split phase takes (one request alone, chunks of one length; at most 256
+ * requests), all of them run in the chunks phase: the splits phase then only
+ * writes the new tokens and the merge launches nothing. */
 int vd_attn_forward_plan(const vd_attn* h, const vd_attn_batch* batch, void* workspace,
                          size_t workspace_bytes, hipStream_t stream);
 int vd_attn_forward_splits(const vd_attn* h, const vd_attn_batch* batch, void* out,

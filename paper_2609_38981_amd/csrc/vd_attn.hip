@@ -2793,16 +2793,22 @@ int check_out_ws(const void* out, bool need_out, const void* ws) {
   return VD_OK;
 }
 
-bool needs_chunks(const vd_attn* h, const vd_attn_batch* b) {
-  return (int64_t)b->max_q_len * h->group > kSplitCols;
-}
-
-// The same from a call's parameters.
+// Some request may have rows for the chunk path.
 bool needs_chunks_params(const Params& P) { return (int64_t)P.max_q * P.G > kSplitCols; }
 
 // Calls of at most kInWaveMaxSeqs requests need no work lists: the split and
 // chunk workgroups derive their items from the lengths.
 bool plans_inwave(const vd_attn_batch* b) { return b->num_seqs <= kInWaveMaxSeqs; }
+
+// Every request has rows for the chunk path: no request has more than
+// max_q_len rows, so even the shortest holds total_q_tokens - (num_seqs - 1)
+// max_q_len of them (one request alone, or chunks of one length).  The call's
+// requests then all take the chunk path, whatever their lengths say
+// (split_cols 0), and the split workgroups and the merge are not launched.
+bool all_chunks(const vd_attn* h, const vd_attn_batch* b) {
+  return plans_inwave(b) &&
+         (b->total_q_tokens - (int64_t)(b->num_seqs - 1) * b->max_q_len) * h->group > kSplitCols;
+}
 
 // The split launch writes the call's new tokens when its workgroups plan for
 // themselves and no split-path request has more than kMaxNewRows query rows
@@ -2815,9 +2821,10 @@ bool fuses_write(const vd_attn* h, const vd_attn_batch* b) {
 }
 
 // The shared-prefix pass runs for calls with the shared_pages hint: at most
-// kCascMaxSeqs requests, no sliding window, contexts of more than one split.
+// kCascMaxSeqs requests, no sliding window, contexts of more than one split, and
+// requests that may be on the split path (its members).
 bool cascades(const vd_attn* h, const vd_attn_batch* b) {
-  return b->shared_pages != 0 && h->window == 0 && b->num_seqs >= 2 &&
+  return b->shared_pages != 0 && h->window == 0 && b->num_seqs >= 2 && !all_chunks(h, b) &&
          b->num_seqs <= kCascMaxSeqs && b->max_context_len > kSplitKeys &&
          b->total_q_tokens * h->group <= INT32_MAX;
 }
@@ -2857,7 +2864,7 @@ Params make_params(const vd_attn* h, const vd_attn_batch* b, void* out, const vo
   P.max_q = b->max_q_len;
   P.max_ctx = b->max_context_len;
   P.max_splits = (b->max_context_len + kSplitKeys - 1) / kSplitKeys;
-  P.split_cols = 16 * split_nb(h, b->max_q_len);
+  P.split_cols = all_chunks(h, b) ? 0 : 16 * split_nb(h, b->max_q_len);
   P.ws_cols = ws_cols(h, b->max_q_len);
   // wide items when every request is on the split path and some may have
   // more than 16 rows (max_q G in 17 .. 32); a call with chunk-path rows keeps
@@ -2886,6 +2893,13 @@ Params make_params(const vd_attn* h, const vd_attn_batch* b, void* out, const vo
 }
 
 int launched() { return hipGetLastError() == hipSuccess ? VD_OK : VD_ERR_LAUNCH; }
+
+// Events of a phase that launches nothing: recorded back to back.
+int record_pair(hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  if (e0 && hipEventRecord(e0, s) != hipSuccess) return VD_ERR_LAUNCH;
+  if (e1 && hipEventRecord(e1, s) != hipSuccess) return VD_ERR_LAUNCH;
+  return VD_OK;
+}
 
 
 
@@ -2923,7 +2937,8 @@ int run_splits(const Params& P0, bool stream_kv, hipStream_t s, hipEvent_t e0 = 
   // 128); a multiple of the dies
   const Geometry geo = device_geometry();
   const int64_t cap = (P.wide && D == 128 ? 8 : 16) * (int64_t)geo.cus;
-  const int64_t split_wgs = (std::min(items, cap) + geo.xcds - 1) / geo.xcds * geo.xcds;
+  const int64_t split_wgs =
+      P.split_cols == 0 ? 0 : (std::min(items, cap) + geo.xcds - 1) / geo.xcds * geo.xcds;
   // the chunk-path requests' new tokens: a workgroup per unit up to the cap
   // (an upper bound of the units: every request's page runs number at most
   // s / 16 + 2, times the KV heads), dispatched after the split workgroups
@@ -2933,6 +2948,7 @@ int run_splits(const Params& P0, bool stream_kv, hipStream_t s, hipEvent_t e0 = 
     append = (std::min(units, cap) + geo.xcds - 1) / geo.xcds * geo.xcds;
   }
   P.append_wgs = (int)append;
+  if (split_wgs + append == 0) return record_pair(s, e0, e1);
   // Calls that can have more items than workgroups take the later ones from
   // a counter in the workspace header, when the items derive their own slots
   // and the K/V stream past the caches (with shared pages, each die keeps its
@@ -2946,7 +2962,7 @@ int run_splits(const Params& P0, bool stream_kv, hipStream_t s, hipEvent_t e0 = 
   const int64_t item_bound = (int64_t)P.num_seqs * P.hkv * req_splits *
                              (!P.wide && (int64_t)P.max_q * P.G > 16 ? 2 : 1);
   P.claim = nullptr;
-  if (P.inwave && stream_kv && !P.casc && item_bound > split_wgs) {
+  if (P.inwave && stream_kv && !P.casc && split_wgs > 0 && item_bound > split_wgs) {
     P.claim = P.casc_hdr + kClaimWord;
     hipLaunchKernelGGL(zero_claim_kernel, dim3(1), dim3(64), 0, s, P.claim);
   }
@@ -2994,7 +3010,10 @@ int run_split_phase(const Params& P, bool stream_kv, hipStream_t s, hipEvent_t e
 
 template <int D>
 int run_merge(const Params& P, hipStream_t s) {
-  const int64_t cols = P.ws_cols;  // = min(max_q * G, split_cols)
+  // contexts of one split are written by the split kernel, chunk-path rows by
+  // the chunk kernel
+  if (P.max_splits <= 1 || P.split_cols == 0) return VD_OK;
+  const int64_t cols = P.ws_cols;
   // the most splits a row folds: every split through the longest context, or
   // with a window of w keys the splits from the one holding p - w + 1 to the
   // one holding p, at most floor((w - 1) / 1024) + 2
@@ -3033,7 +3052,7 @@ int run_chunks(const Params& P, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent
   // items a second round of pairs takes as long as the chunk kernel, which
   // runs two workgroups on a CU (calls, us, chunk kernel against pairs: a
   // 1000-token chunk at key 30000, 252 items of the chunk kernel, 748 / 910; 512
-  // tokens, 128 items, 671 / 438; 64 tokens at key 8000, 16 items, 190 / 121).
+  // tokens, 128 items, 671 / 438; 64 tokens at key 8000, 16 items, 182 / 121).
   if (P.inwave && P.max_splits > 1 && items(kPairCols) <= device_geometry().cus) {
     constexpr size_t lds = chunk_pair_lds_bytes<D>();
     const auto kern = P.window > 0 ? &chunk_pair_kernel<D, true> : &chunk_pair_kernel<D, false>;
@@ -3077,6 +3096,43 @@ void* scratch_address() {
 
 bool ws_ok(const vd_attn* h, const vd_attn_batch* b, const void* ws, size_t bytes) {
   return ws && bytes >= ws_layout(h, b->num_seqs, b->max_q_len, b->max_context_len).total;
+}
+
+// The checks of a call or phase, and its kernels' parameters.  False: the call
+// ends here with rc (an error, or VD_OK for a call without rows).
+bool begin_call(const vd_attn* h, const vd_attn_batch* b, void* out, bool need_out, const void* ws,
+                size_t ws_bytes, Params& P, int& rc) {
+  rc = check_batch(h, b);
+  if (rc != VD_OK || b->num_seqs == 0 || b->total_q_tokens == 0) return false;
+  if ((rc = check_out_ws(out, need_out, ws)) != VD_OK) return false;
+  if (!ws_ok(h, b, ws, ws_bytes)) {
+    rc = VD_ERR_WORKSPACE;
+    return false;
+  }
+  P = make_params(h, b, out, ws);
+  return true;
+}
+
+int phase_plan(const vd_attn* h, const vd_attn_batch* b, const Params& P, hipStream_t s) {
+  if (!needs_plan(h, b)) return VD_OK;  // the split workgroups plan for themselves
+  return h->d == 64 ? run_plan<64>(P, s) : run_plan<128>(P, s);
+}
+
+int phase_splits(const vd_attn* h, const vd_attn_batch* b, const Params& P, hipStream_t s,
+                 hipEvent_t e0, hipEvent_t e1) {
+  // with the shared-prefix pass, the shared splits are read (cached) by the
+  // shared-prefix kernel and the split items stream the requests' own pages
+  const bool nt = b->shared_pages == 0 || P.casc;
+  return h->d == 64 ? run_split_phase<64>(P, nt, s, e0, e1) : run_split_phase<128>(P, nt, s, e0, e1);
+}
+
+int phase_chunks(const vd_attn* h, const Params& P, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  if (!needs_chunks_params(P)) return record_pair(s, e0, e1);
+  return h->d == 64 ? run_chunks<64>(P, s, e0, e1) : run_chunks<128>(P, s, e0, e1);
+}
+
+int phase_merge(const vd_attn* h, const Params& P, hipStream_t s) {
+  return h->d == 64 ? run_merge<64>(P, s) : run_merge<128>(P, s);
 }
 
 }  // namespace
@@ -3125,99 +3181,61 @@ int vd_attn_workspace_size(const vd_attn* h, int32_t num_seqs, int32_t max_q_len
 
 int vd_attn_forward_plan(const vd_attn* h, const vd_attn_batch* b, void* workspace,
                          size_t workspace_bytes, hipStream_t stream) {
-  int rc = check_batch(h, b);
-  if (rc != VD_OK || b->num_seqs == 0 || b->total_q_tokens == 0) return rc;
-  if ((rc = check_out_ws(nullptr, false, workspace)) != VD_OK) return rc;
-  if (!ws_ok(h, b, workspace, workspace_bytes)) return VD_ERR_WORKSPACE;
-  if (!needs_plan(h, b)) return VD_OK;  // the split workgroups plan for themselves
-  const Params P = make_params(h, b, nullptr, workspace);
-  return h->d == 64 ? run_plan<64>(P, stream) : run_plan<128>(P, stream);
+  Params P;
+  int rc;
+  if (!begin_call(h, b, nullptr, false, workspace, workspace_bytes, P, rc)) return rc;
+  return phase_plan(h, b, P, stream);
 }
 
 int vd_attn_forward_splits(const vd_attn* h, const vd_attn_batch* b, void* out, void* workspace,
                            size_t workspace_bytes, hipStream_t stream) {
-  int rc = check_batch(h, b);
-  if (rc != VD_OK || b->num_seqs == 0 || b->total_q_tokens == 0) return rc;
-  if ((rc = check_out_ws(out, true, workspace)) != VD_OK) return rc;
-  if (!ws_ok(h, b, workspace, workspace_bytes)) return VD_ERR_WORKSPACE;
-  const Params P = make_params(h, b, out, workspace);
-  // with the shared-prefix pass, the shared splits are read (cached) by the
-  // shared-prefix kernel and the split items stream the requests' own pages
-  const bool nt = b->shared_pages == 0 || P.casc;
-  return h->d == 64 ? run_split_phase<64>(P, nt, stream) : run_split_phase<128>(P, nt, stream);
+  return vd_attn_forward_splits_timed(h, b, out, workspace, workspace_bytes, stream, nullptr,
+                                      nullptr);
 }
 
 int vd_attn_forward_chunks(const vd_attn* h, const vd_attn_batch* b, void* out,
                            const void* workspace, size_t workspace_bytes, hipStream_t stream) {
-  int rc = check_batch(h, b);
-  if (rc != VD_OK || b->num_seqs == 0 || b->total_q_tokens == 0) return rc;
-  if ((rc = check_out_ws(out, true, workspace)) != VD_OK) return rc;
-  if (!ws_ok(h, b, workspace, workspace_bytes)) return VD_ERR_WORKSPACE;
-  if (!needs_chunks(h, b)) return VD_OK;
-  const Params P = make_params(h, b, out, workspace);
-  return h->d == 64 ? run_chunks<64>(P, stream) : run_chunks<128>(P, stream);
-}
-
-// Events of a phase that launches nothing: recorded back to back.
-static int record_pair(hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  if (e0 && hipEventRecord(e0, s) != hipSuccess) return VD_ERR_LAUNCH;
-  if (e1 && hipEventRecord(e1, s) != hipSuccess) return VD_ERR_LAUNCH;
-  return VD_OK;
+  return vd_attn_forward_chunks_timed(h, b, out, workspace, workspace_bytes, stream, nullptr,
+                                      nullptr);
 }
 
 int vd_attn_forward_splits_timed(const vd_attn* h, const vd_attn_batch* b, void* out,
                                  void* workspace, size_t workspace_bytes, hipStream_t stream,
                                  hipEvent_t start, hipEvent_t stop) {
-  int rc = check_batch(h, b);
-  if (rc != VD_OK) return rc;
-  if (b->num_seqs == 0 || b->total_q_tokens == 0) return record_pair(stream, start, stop);
-  if ((rc = check_out_ws(out, true, workspace)) != VD_OK) return rc;
-  if (!ws_ok(h, b, workspace, workspace_bytes)) return VD_ERR_WORKSPACE;
-  const Params P = make_params(h, b, out, workspace);
-  // with the shared-prefix pass, the shared splits are read (cached) by the
-  // shared-prefix kernel and the split items stream the requests' own pages
-  const bool nt = b->shared_pages == 0 || P.casc;
-  return h->d == 64 ? run_split_phase<64>(P, nt, stream, start, stop)
-                    : run_split_phase<128>(P, nt, stream, start, stop);
+  Params P;
+  int rc;
+  if (!begin_call(h, b, out, true, workspace, workspace_bytes, P, rc))
+    return rc == VD_OK ? record_pair(stream, start, stop) : rc;
+  return phase_splits(h, b, P, stream, start, stop);
 }
 
 int vd_attn_forward_chunks_timed(const vd_attn* h, const vd_attn_batch* b, void* out,
                                  const void* workspace, size_t workspace_bytes,
                                  hipStream_t stream, hipEvent_t start, hipEvent_t stop) {
-  int rc = check_batch(h, b);
-  if (rc != VD_OK) return rc;
-  if (b->num_seqs == 0 || b->total_q_tokens == 0) return record_pair(stream, start, stop);
-  if ((rc = check_out_ws(out, true, workspace)) != VD_OK) return rc;
-  if (!ws_ok(h, b, workspace, workspace_bytes)) return VD_ERR_WORKSPACE;
-  if (!needs_chunks(h, b)) return record_pair(stream, start, stop);
-  const Params P = make_params(h, b, out, workspace);
-  return h->d == 64 ? run_chunks<64>(P, stream, start, stop)
-                    : run_chunks<128>(P, stream, start, stop);
+  Params P;
+  int rc;
+  if (!begin_call(h, b, out, true, workspace, workspace_bytes, P, rc))
+    return rc == VD_OK ? record_pair(stream, start, stop) : rc;
+  return phase_chunks(h, P, stream, start, stop);
 }
 
 int vd_attn_forward_merge(const vd_attn* h, const vd_attn_batch* b, void* out,
                           const void* workspace, size_t workspace_bytes, hipStream_t stream) {
-  int rc = check_batch(h, b);
-  if (rc != VD_OK || b->num_seqs == 0 || b->total_q_tokens == 0) return rc;
-  if ((rc = check_out_ws(out, true, workspace)) != VD_OK) return rc;
-  if (!ws_ok(h, b, workspace, workspace_bytes)) return VD_ERR_WORKSPACE;
-  const Params P = make_params(h, b, out, workspace);
-  return h->d == 64 ? run_merge<64>(P, stream) : run_merge<128>(P, stream);
+  Params P;
+  int rc;
+  if (!begin_call(h, b, out, true, workspace, workspace_bytes, P, rc)) return rc;
+  return phase_merge(h, P, stream);
 }
 
 int vd_attn_forward(const vd_attn* h, const vd_attn_batch* b, void* out, void* workspace,
                     size_t workspace_bytes, hipStream_t stream) {
-  int rc = check_batch(h, b);
-  if (rc != VD_OK || b->num_seqs == 0 || b->total_q_tokens == 0) return rc;
-  if ((rc = check_out_ws(out, true, workspace)) != VD_OK) return rc;
-  if (!ws_ok(h, b, workspace, workspace_bytes)) return VD_ERR_WORKSPACE;
-  rc = vd_attn_forward_plan(h, b, workspace, workspace_bytes, stream);
-  if (rc != VD_OK) return rc;
-  rc = vd_attn_forward_splits(h, b, out, workspace, workspace_bytes, stream);
-  if (rc != VD_OK) return rc;
-  rc = vd_attn_forward_chunks(h, b, out, workspace, workspace_bytes, stream);
-  if (rc != VD_OK) return rc;
-  return vd_attn_forward_merge(h, b, out, workspace, workspace_bytes, stream);
+  Params P;
+  int rc;
+  if (!begin_call(h, b, out, true, workspace, workspace_bytes, P, rc)) return rc;
+  if ((rc = phase_plan(h, b, P, stream)) != VD_OK) return rc;
+  if ((rc = phase_splits(h, b, P, stream, nullptr, nullptr)) != VD_OK) return rc;
+  if ((rc = phase_chunks(h, P, stream, nullptr, nullptr)) != VD_OK) return rc;
+  return phase_merge(h, P, stream);
 }
 
 int vd_attn_forward_noalloc(const vd_attn* h, const vd_attn_batch* b, void* out,

@@ -13,6 +13,7 @@ import numpy as np
 import pytest
 import torch
 
+from paper_2609_38981_amd import staging as S
 from paper_2609_38981_amd import vdattn as V
 from paper_2609_38981_amd import workloads as W
 from tests import gpu_util as U
@@ -301,3 +302,29 @@ def test_paired_chunks_equal_chunks(shape, n, s):
     assert np.array_equal(a, b[other.length:]) and np.array_equal(la, lb[other.length:])
     U.assert_written(U.by_position(alone, a))
     U.parity(alone, a, rows=[0, s // 2, s - 1])
+
+
+@pytest.mark.parametrize("shape", [W.LLAMA8B, W.TINY], ids=["d128", "d64"])
+@pytest.mark.parametrize("append", [False, True], ids=["written", "append"])
+def test_calls_of_prefill_rows_only(shape, append):
+    """Calls whose sizes rule the split path out (one chunk; chunks of one
+    length) run without it: the same bits as beside a decode row, new tokens
+    written or handed over; and a request with fewer rows than total_q_tokens
+    and max_q_len promise still gets its output."""
+    rng = W.rng_for(72, 4)
+    ps = [W.make_prompt(shape, n, 72, i, q_window=60) for i, n in enumerate([1100, 700, 60, 300])]
+    decode = [W.Req(3, 300, 1)]
+    for reqs in ([W.Req(0, 1100, 60)], [W.Req(i, ps[i].length, 40) for i in range(3)]):
+        alone, mixed = W.place(shape, ps, reqs, rng), W.place(shape, ps, reqs + decode, rng)
+        a, la = U.gpu_run(alone, append=append, with_lse=True)
+        b, lb = U.gpu_run(mixed, append=append, with_lse=True)
+        assert np.array_equal(a, b[:-1]) and np.array_equal(la, lb[:-1])
+        U.assert_written(U.by_position(alone, a))
+    one = W.place(shape, ps, decode, rng)
+    want = U.gpu_run(one)
+    attn = U.handle(shape)
+    b = S.to_device(attn, one).batch
+    b.q = torch.cat([b.q] * 40)
+    b.max_q_len = 40
+    got = S.bits_of(attn.forward(b))
+    assert np.array_equal(got[:1], want)
