@@ -1590,6 +1590,257 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NA == 1 || D
   }
 }
 
+// ---------------------------------------------------------------------------
+// shared-out split kernel: the split kernel's items for calls with few of them
+// (run_splits has the rule), one workgroup of 8 wavefronts per item.  A
+// wavefront of the split kernel walks its split's tiles one after the other, one
+// tile's loads ahead: 25 us for the step of one request of 1900 keys, nearly all
+// of it latency.  Here every load of the split is in flight at once (256 KB
+// at head_dim 128), and the tiles' work is shared out: each wavefront runs Q.K
+// and the weights of two tiles, then one d-block of every P.V.  What is
+// sequential in the update is carried through LDS: the tile maxima give every
+// tile its running maximum (exact), the weights and alphas feed each d-block's
+// chain over the tiles in ascending order -- per column the operations of
+// split_item, in its order.  Much of what is left is the instruction fetch of
+// code that runs once: with the code for the request's end (new rows, masked
+// keys) in all 16 unrolled tiles instead of the last two the kernel was 100 KB
+// and the call took 23.4 us, now 18.5 (28.6 with the split kernel).
+// ---------------------------------------------------------------------------
+constexpr int kShareWaves = 8;
+
+// Masked maximum of a column's scores over one tile (tile_softmax's).
+template <bool WIN>
+__device__ __forceinline__ float tile_max(const f32x4 (&acc)[kPagesPerTile], int j0, int p, int lo,
+                                          float c) {
+  const int grp = __lane_id() >> 4;
+  float mx = -__builtin_inff();
+#pragma unroll
+  for (int b = 0; b < kPagesPerTile; ++b)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int key = j0 + 16 * b + 4 * grp + i;
+      const float g = acc[b][i] * c;
+      mx = fmax_(mx, key <= p && (!WIN || key >= lo) ? g : -__builtin_inff());
+    }
+  return column_max(mx);
+}
+
+template <int D, bool WIN, bool NT>
+__global__ __launch_bounds__(64 * kShareWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void split_share_kernel(Params P) {
+  constexpr int NX = kTilesPerSplit, MB = D / 16, BLK = kPage * D;
+  static_assert(MB <= kShareWaves && NX == 2 * kShareWaves, "work shares");
+  static_assert(kMaxNewRows <= kTileKeys, "new rows lie in a request's last two tiles");
+  __shared__ __attribute__((aligned(16))) uint16_t pw[NX][64][16];  // P.V operands of every tile
+  __shared__ float tmax[NX][16], talpha[NX][16], tsum[NX][16];
+  __shared__ int hist[kShareWaves][kTilesPerSplit + 1];
+  const int wave = uni(threadIdx.x >> 6);
+  SplitRef it;
+  if (!inwave_split_item(P, blockIdx.x, it, hist[wave])) return;
+  const int r = uni(it.r), g = it.g, k = it.k, half = it.half;
+  const Req R = it.R;
+  const int window = WIN ? P.window : 0;
+  const int lane = __lane_id();
+  const int col = lane & 15, grp = lane >> 4;
+  const int c = 16 * half + col;
+  const bool live = c < R.s * P.G;
+  const int pos = live ? R.n - R.s + c / P.G : -1;
+  const int lo = window_lo(pos, window);
+  const int kt0 = k * kTilesPerSplit;
+  const int kt_first = max(kt0, window_lo(R.n - R.s, window) / kTileKeys);
+  const int nt = min(kt0 + kTilesPerSplit, (R.n + kTileKeys - 1) / kTileKeys) - kt_first;
+  // lane l: the block offset of the split's l-th page from kt_first, -1 past the
+  // request's pages or for an id outside the pool
+  const int lp = kt_first * kPagesPerTile + lane;
+  int page = lp < (R.n + kPage - 1) / kPage ? P.pt[(int64_t)r * P.pt_stride + lp] : -1;
+  if (page >= P.num_pages) page = -1;
+  u16x8 qf[1][D / 32];
+  load_q<D>(P, qf[0], R.q0 + (live ? c / P.G : 0), g * P.G + (live ? c % P.G : 0), live);
+  const int64_t off = page < 0 ? -1 : (int64_t)page * P.hkv + g;
+  const uint64_t bad = __ballot(page < 0);
+  auto page_off = [&](int i) {
+    const uint32_t l = __builtin_amdgcn_readlane((int)(uint32_t)off, i);
+    const uint32_t h = __builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)off >> 32), i);
+    return (int64_t)(((uint64_t)h << 32) | l);
+  };
+  auto tile_pages = [&](int x, int64_t (&pb)[kPagesPerTile]) {
+#pragma unroll
+    for (int b = 0; b < kPagesPerTile; ++b) pb[b] = page_off(x * kPagesPerTile + b);
+  };
+  // The request's end (new rows, keys past n) reaches the split's last two tiles
+  // at most; "special" tiles nt - 2 and nt - 1 have their own code.  Wavefront
+  // w's first tile is the w-th from the end, its second the (w + 8)-th.
+  auto has_new = [&](int kt) { return P.fuse_write && (kt + 1) * kTileKeys > R.n - R.s; };
+  const int xa = nt - 1 - wave, xb = xa - kShareWaves;
+  const bool has_block = wave < MB;
+  u16x8 kf[kPagesPerTile][D / 32];
+  auto load_v_tile = [&](int x, u16x4 (&v)[kPagesPerTile]) {
+#pragma unroll
+    for (int b = 0; b < kPagesPerTile; ++b) {
+      const int64_t o = page_off(x * kPagesPerTile + b);
+      v[b] = load_kv<NT, u16x4>(P.vpool + (o < 0 ? 0 : o) * BLK + 256 * wave + 4 * lane);
+    }
+  };
+  if (xa >= 0) {
+    int64_t pb[kPagesPerTile];
+    tile_pages(xa, pb);
+    const int kt = kt_first + xa;
+    if (has_new(kt))
+      load_k_new<D, NT>(P, pb, kf, kt * kTileKeys, g, R);
+    else
+      load_k<D, NT>(P, pb, kf);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  // V of d-block `wave`: tiles 0 .. nt - 3, then the special ones
+  u16x4 vh[NX - 2][kPagesPerTile], ve[2][kPagesPerTile];
+  if (has_block) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+      if (nt - 2 + e >= 0) load_v_tile(nt - 2 + e, ve[e]);
+#pragma unroll
+    for (int x = 0; x < NX / 2; ++x)
+      if (x < nt - 2) load_v_tile(x, vh[x]);
+  }
+  f32x4 acc[2][1][kPagesPerTile];
+  auto score = [&](int x, f32x4 (&a)[1][kPagesPerTile]) {
+    tile_scores<D, 1>([&](int b, int ks) { return kf[b][ks]; }, qf, a);
+    const float mx = tile_max<WIN>(a[0], (kt_first + x) * kTileKeys, pos, lo, P.c);
+    if (grp == 0) tmax[x][col] = mx;
+  };
+  if (xa >= 0) {
+    const int kt = kt_first + xa, j0 = kt * kTileKeys;
+    int64_t pb[kPagesPerTile];
+    tile_pages(xa, pb);
+    if (has_new(kt) && half == 0) store_k_new<D>(P, pb, kf, j0, R);
+    if (j0 + kTileKeys > R.n || ((bad >> (xa * kPagesPerTile)) & 15) != 0) mask_k<D>(pb, j0, R.n, kf);
+    score(xa, acc[0]);
+  }
+  if (xb >= 0) {
+    int64_t pb[kPagesPerTile];
+    tile_pages(xb, pb);
+    load_k<D, NT>(P, pb, kf);
+    __builtin_amdgcn_sched_barrier(0);
+    if (has_block) {
+#pragma unroll
+      for (int x = NX / 2; x < NX - 2; ++x)
+        if (x < nt - 2) load_v_tile(x, vh[x]);
+    }
+    if (((bad >> (xb * kPagesPerTile)) & 15) != 0)
+      mask_k<D>(pb, (kt_first + xb) * kTileKeys, R.n, kf);
+    score(xb, acc[1]);
+  } else if (has_block) {
+#pragma unroll
+    for (int x = NX / 2; x < NX - 2; ++x)
+      if (x < nt - 2) load_v_tile(x, vh[x]);
+  }
+  __syncthreads();
+  // the weights of those tiles, from the column's running maximum before each
+  auto sees = [&](int x) {
+    const int j0 = (kt_first + x) * kTileKeys;
+    return j0 <= pos && (!WIN || j0 + kTileKeys - 1 >= lo);
+  };
+  float m = -__builtin_inff();
+  auto run_max = [&](int x0, int x1) {
+    for (int x = x0; x < x1; ++x) m = sees(x) ? fmax_(m, tmax[x][col]) : m;
+  };
+  auto put_weights = [&](int x, const TileWeights& w) {
+    *reinterpret_cast<u16x8*>(&pw[x][lane][0]) = w.pf[0];
+    *reinterpret_cast<u16x8*>(&pw[x][lane][8]) = w.pf[1];
+    if (grp == 0) {
+      talpha[x][col] = w.alpha;
+      tsum[x][col] = w.z_new;  // from z = 0: the tile's sum
+    }
+  };
+  State<D> st;
+  st.z = 0.0f;
+  if (xb >= 0) {
+    // at least 8 tiles before the request's end: every key is at or before
+    // every row's position
+    run_max(0, xb);
+    st.m = m;
+    put_weights(xb, tile_softmax<D, WIN, WIN>(st, acc[1][0], (kt_first + xb) * kTileKeys,
+                                              WIN ? pos : 0, lo, P.c));
+  }
+  if (xa >= 0) {
+    run_max(max(xb, 0), xa);
+    st.m = m;
+    put_weights(xa, tile_softmax<D, true, WIN>(st, acc[0][0], (kt_first + xa) * kTileKeys, pos, lo, P.c));
+  }
+  __syncthreads();
+  // P.V of d-block `wave`, tiles ascending; (m, z) in every wavefront
+  if (!has_block) return;
+  m = -__builtin_inff();
+  float z = 0.0f;
+  f32x4 u = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto pv = [&](int x, const u16x4 (&v)[kPagesPerTile]) {
+    const float alpha = talpha[x][col];
+    const u16x8 p0 = *reinterpret_cast<const u16x8*>(&pw[x][lane][0]);
+    const u16x8 p1 = *reinterpret_cast<const u16x8*>(&pw[x][lane][8]);
+    u = u * alpha;
+    u = mfma(cat4(v[0], v[1]), p0, u);
+    u = mfma(cat4(v[2], v[3]), p1, u);
+    const bool h = sees(x);
+    z = h ? z * alpha + tsum[x][col] : z;
+    m = h ? fmax_(m, tmax[x][col]) : m;
+  };
+#pragma unroll
+  for (int x = 0; x < NX - 2; ++x)
+    if (x < nt - 2) {
+      if (bad != 0) {  // (pages past the request's end, or invalid ids)
+#pragma unroll
+        for (int b = 0; b < kPagesPerTile; ++b)
+          if ((bad >> (x * kPagesPerTile + b)) & 1) vh[x][b] = u16x4{0, 0, 0, 0};
+      }
+      pv(x, vh[x]);
+    }
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const int x = nt - 2 + e, kt = kt_first + x, j0 = kt * kTileKeys;
+    if (x < 0) continue;
+    int64_t pb[kPagesPerTile];
+    tile_pages(x, pb);
+    if (has_new(kt)) {
+      // the call's new V rows: from v_new, and to their pool slots
+#pragma unroll
+      for (int b = 0; b < kPagesPerTile; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int key = j0 + 16 * b + 4 * grp + i;
+          if (is_new_key(key, R)) {
+            const uint16_t v =
+                P.vnew[((int64_t)(R.q0 + key - (R.n - R.s)) * P.hkv + g) * D + 16 * wave + col];
+            ve[e][b][i] = v;
+            if (half == 0 && pb[b] >= 0)
+              const_cast<uint16_t*>(P.vpool)[pb[b] * BLK + 256 * wave + 4 * lane + i] = v;
+          }
+        }
+    }
+    if (j0 + kTileKeys > R.n || ((bad >> (x * kPagesPerTile)) & 15) != 0) {
+#pragma unroll
+      for (int b = 0; b < kPagesPerTile; ++b)
+        ve[e][b] = pb[b] >= 0 ? mask4(ve[e][b], j0 + 16 * b + 4 * grp, R.n) : u16x4{0, 0, 0, 0};
+    }
+    pv(x, ve[e]);
+  }
+  if (pos < 0) return;
+  if (request_splits(R, window) == 1) {
+    const float rho = final_scale(z);
+    const int64_t row = (int64_t)(R.q0 + c / P.G) * P.hq + g * P.G + c % P.G;
+    if (P.lse && wave == 0 && grp == 0) P.lse[row] = final_lse(m, z);
+    u16x4 v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = bf16_out(u[i] * rho);
+    *reinterpret_cast<u16x4*>(P.out + row * D + 16 * wave + 4 * grp) = v;
+    return;
+  }
+  if (k > pos / kSplitKeys || k < lo / kSplitKeys) return;
+  const int64_t pidx = ((int64_t)(r * P.hkv + g) * P.ws_cols + c) * P.max_splits + k;
+  if (wave == 0 && grp == 0) {
+    P.ws_m[pidx] = m;
+    P.ws_z[pidx] = z;
+  }
+  *reinterpret_cast<f32x4*>(P.ws_u + pidx * D + 16 * wave + 4 * grp) = u;
+}
+
 // Zeroes the split launch's slot counter (a kernel rather than a memset, so
 // that a captured graph replays it like the launches around it).
 __global__ __launch_bounds__(64) void zero_claim_kernel(int32_t* claim) {
@@ -2922,6 +3173,11 @@ auto split_kernel_for(const Params& P) {
   return P.window > 0 ? &split_kernel<D, true, NT, 1> : &split_kernel<D, false, NT, 1>;
 }
 
+template <int D, bool NT>
+auto split_share_kernel_for(const Params& P) {
+  return P.window > 0 ? &split_share_kernel<D, true, NT> : &split_share_kernel<D, false, NT>;
+}
+
 template <int D>
 int run_splits(const Params& P0, bool stream_kv, hipStream_t s, hipEvent_t e0 = nullptr,
                hipEvent_t e1 = nullptr) {
@@ -2961,6 +3217,23 @@ int run_splits(const Params& P0, bool stream_kv, hipStream_t s, hipEvent_t e0 = 
                    : P.max_splits;
   const int64_t item_bound = (int64_t)P.num_seqs * P.hkv * req_splits *
                              (!P.wide && (int64_t)P.max_q * P.G > 16 ? 2 : 1);
+  const int64_t shared_items =
+      (int64_t)P.num_seqs * P.hkv * req_splits * ((int64_t)P.max_q * P.G > 16 ? 2 : 1);
+  // Few items: a workgroup per item (one fits a CU at a time), when each finds
+  // a CU of its own and contexts are longer than two tiles.  Calls, us, split
+  // kernel against shared-out items: 1 request of 1900 keys 28.6 / 18.5, 16 of
+  // 2000 (256 items) 33.9 / 32.0, 4 of 1700 verifying 4 tokens at 8 query heads
+  // per KV head 44.4 / 22.5; in two rounds, 16 of 4000 keys, 45.9 / 64.3; two
+  // tiles (the smallest call) 8.2 / 8.6.
+  if (P.inwave && !P.casc && split_wgs > 0 && append == 0 && shared_items <= geo.cus &&
+      P.max_ctx > 2 * kTileKeys) {
+    P.wide = 0;  // 16-row items
+    P.claim = nullptr;
+    const dim3 wgs((unsigned)((shared_items + geo.xcds - 1) / geo.xcds * geo.xcds));
+    const auto kern = stream_kv ? split_share_kernel_for<D, true>(P) : split_share_kernel_for<D, false>(P);
+    hipExtLaunchKernelGGL(kern, wgs, dim3(64 * kShareWaves), 0, s, e0, e1, 0, P);
+    return launched();
+  }
   P.claim = nullptr;
   if (P.inwave && stream_kv && !P.casc && split_wgs > 0 && item_bound > split_wgs) {
     P.claim = P.casc_hdr + kClaimWord;

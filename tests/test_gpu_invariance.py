@@ -328,3 +328,64 @@ def test_calls_of_prefill_rows_only(shape, append):
     b.max_q_len = 40
     got = S.bits_of(attn.forward(b))
     assert np.array_equal(got[:1], want)
+
+
+SHARE_SHAPES = [W.LLAMA8B, W.LLAMA70B, W.Shape(8, 8, 64), W.Shape(21, 3, 64, window=700),
+                W.Shape(32, 8, 128, window=1100)]
+
+
+@pytest.mark.parametrize("shape", SHARE_SHAPES, ids=["d128-g4", "d128-g8", "d64-g1", "d64-g7-window",
+                                                     "d128-window"])
+@pytest.mark.parametrize("append", [False, True], ids=["written", "append"])
+@pytest.mark.parametrize("s", [1, 4])
+def test_shared_out_splits_equal_splits(shape, append, s):
+    """Decode and verify rows in calls of one request (few items: a workgroup per
+    split) equal, bit for bit, in output, log-sum-exp and the new tokens' pool
+    slots, the same rows in a call of 70 requests (a wavefront per split):
+    contexts of 3 tiles, at split and tile edges, with new tokens on both sides of
+    a tile or split edge; and match the oracle."""
+    ns = [129, 577, 1024, 1025, 1026, 1100, 1984, 2050, 3071, 4096 + 64]
+    ps = [W.make_prompt(shape, n, 73, n, q_window=s) for n in ns]
+    ps += [W.make_prompt(shape, 100 + i, 73, i, q_window=1) for i in range(60)]
+    rng = W.rng_for(73, 4)
+    reqs = [W.Req(i, p.length, s if i < len(ns) else 1) for i, p in enumerate(ps)]
+    big = W.place(shape, ps, reqs, rng)
+    want, lse = U.gpu_run(big, append=append, with_lse=True)
+    U.assert_written(U.by_position(big, want))
+    for i, n in enumerate(ns):
+        one = big.subcall([i])
+        got, l1 = U.gpu_run(one, append=append, with_lse=True)
+        row = big.row_of(i, n - s)
+        assert np.array_equal(got, want[row:row + s]), n
+        assert np.array_equal(l1, lse[row:row + s]), n
+        if append:
+            attn = U.handle(shape)
+            a = S.to_device(attn, one, append=True).batch
+            b = S.to_device(attn, one, append=False).batch
+            attn.forward(a)
+            assert torch.equal(a.k_pool.view(torch.int16), b.k_pool.view(torch.int16)), n
+            assert torch.equal(a.v_pool.view(torch.int16), b.v_pool.view(torch.int16)), n
+    U.parity(big, want, rows=[big.row_of(i, n - 1) for i, n in enumerate(ns)])
+
+
+def test_shared_out_splits_read_invalid_pages_as_zeros():
+    """A page id outside the pool, in the first tiles, the last ones and the
+    tile of the new token, reads as zeros in the shared-out kernel as in the
+    split kernel."""
+    shape = W.LLAMA8B
+    ps = [W.make_prompt(shape, 1800, 74, i, q_window=1) for i in range(40)]
+    call = W.place(shape, ps, [W.Req(i, 1800, 1) for i in range(40)], W.rng_for(74, 4))
+    attn = U.handle(shape)
+    b = S.to_device(attn, call, append=True, poison=False).batch
+    for page, bad in ((3, -1), (40, call.num_pages), (75, -7), (112, 2**31 - 1)):
+        b.page_table[:, page] = bad
+    want = attn.forward(b)
+    one = S.to_device(attn, call, append=True, poison=False).batch
+    one = S.Batch(q=b.q[:1].contiguous(), cu_q_lens=b.cu_q_lens[:2].contiguous(),
+                  context_lens=b.context_lens[:1].contiguous(),
+                  page_table=b.page_table[:1].contiguous(), k_pool=one.k_pool, v_pool=one.v_pool,
+                  num_pages=call.num_pages, max_q_len=1, max_context_len=1800,
+                  k_new=b.k_new[:1].contiguous(), v_new=b.v_new[:1].contiguous())
+    got = attn.forward(one)
+    assert np.array_equal(S.bits_of(got), S.bits_of(want)[:1])
+    assert np.isfinite(W.bf16_to_f32(S.bits_of(got))).all()
