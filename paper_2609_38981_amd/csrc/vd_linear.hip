@@ -45,12 +45,15 @@ namespace {
 constexpr int kKStep = 64;  // K is a multiple of this
 constexpr int kGroupM = 4;  // row tiles per group of the tile order
 
-// One tile shape: kWM x kWN wavefronts, each computing XB x YB MFMA blocks of
+// One tile shape: WM x WN wavefronts, each computing XB x YB MFMA blocks of
 // 16 x 16; K advances BK per step through an LDS ring of ST stages; EU is the
-// wavefronts per SIMD the registers are budgeted for.
-template <int WM_, int WN_, int XB_, int YB_, int BK_, int ST_, int EU_>
+// wavefronts per SIMD the registers are budgeted for.  LATE: half of a step's
+// copies are issued after the first products instead of before them (a CU
+// takes 64 bytes a cycle, and the whole burst holds up the wavefront).
+template <int WM_, int WN_, int XB_, int YB_, int BK_, int ST_, int EU_, bool LATE_>
 struct Tile {
   static constexpr int WM = WM_, WN = WN_, XB = XB_, YB = YB_, BK = BK_, ST = ST_, EU = EU_;
+  static constexpr bool LATE = LATE_;
   static constexpr int kWaves = WM * WN, kThreads = 64 * kWaves;
   static constexpr int BM = WM * 16 * XB;         // rows of a (tokens) per workgroup tile
   static constexpr int BN = WN * 16 * YB;         // rows of b (output features) per tile
@@ -137,18 +140,20 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
   }
   const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
   const int steps = (K + BK - 1) / BK;
-  auto fetch = [&](int step) {
+  // copies first .. last - 1 of this wavefront's share of a step
+  auto fetch = [&](int step, int first, int last) {
     const int k0 = step * BK;
     const uint32_t st = lds0 + (step % ST) * T::kStage;
     if (BK == kKStep || k0 + BK <= K) {
 #pragma unroll
       for (int j = 0; j < T::kCopies; ++j)
-        lds_dma16(src[j] + k0, uni((int)(st + 1024 * copy_of(j))));
+        if (j >= first && j < last) lds_dma16(src[j] + k0, uni((int)(st + 1024 * copy_of(j))));
     } else {
       // the ragged last step: chunks past K repeat the row's last one (never used)
 #pragma unroll
       for (int j = 0; j < T::kCopies; ++j)
-        lds_dma16(src[j] - ck[j] + min(k0 + ck[j], K - 8), uni((int)(st + 1024 * copy_of(j))));
+        if (j >= first && j < last)
+          lds_dma16(src[j] - ck[j] + min(k0 + ck[j], K - 8), uni((int)(st + 1024 * copy_of(j))));
     }
   };
 
@@ -166,12 +171,14 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
   // copies of step t + ST - 1 then refill while step t is computed.
 #pragma unroll
   for (int t = 0; t < ST - 1; ++t)
-    if (t < steps) fetch(t);
+    if (t < steps) fetch(t, 0, T::kCopies);
   for (int t = 0; t < steps; ++t) {
     const int later = steps - 1 - t;
     wait_stages<T::kCopies, ST - 2>(later);  // this wavefront's copies of step t have landed
     lds_barrier();
-    if (t + ST - 1 < steps) fetch(t + ST - 1);
+    constexpr int early = T::LATE ? T::kCopies / 2 : T::kCopies;
+    const bool more = t + ST - 1 < steps;
+    if (more) fetch(t + ST - 1, 0, early);
     const char* TA = reinterpret_cast<const char*>(lds) + (t % ST) * T::kStage;
     const char* TB = TA + T::kTileA;
     auto chunk = [&](int kc) {
@@ -192,8 +199,12 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
     };
     if (BK == kKStep || (t + 1) * BK <= K) {
 #pragma unroll
-      for (int kc = 0; kc < BK / 32; ++kc) chunk(kc);
+      for (int kc = 0; kc < BK / 32; ++kc) {
+        chunk(kc);
+        if (T::LATE && kc == 0 && more) fetch(t + ST - 1, early, T::kCopies);
+      }
     } else {
+      // (the ragged last step: no copies are left)
       for (int kc = 0; kc < (K - t * BK) / 32; ++kc) chunk(kc);
     }
   }
@@ -242,22 +253,26 @@ int launch(const Call& x) {
 // fills the chip wins over a larger one that leaves CUs idle and over a
 // smaller one that needs a second round or reads its operands more often.
 // Measured at K = 4096 (us; the 256 x 192 shape, used for every call before,
-// in brackets): 1 x 6144 12.0 [70.9], 32 x 6144 14.1 [71.7], 48 x 6144 16.6
+// in brackets): 1 x 6144 12.0 [70.9], 32 x 6144 14.1 [71.7], 48 x 6144 16.0
 // [72.4], 100 x 6144 20.0 [74.4], 200 x 6144 23.3 [81.1], 300 x 6144 29.7
-// [75.6], 512 x 6144 37.6 [86.6], 1024 x 6144 52.8 [86.2], 4096 x 1024 38.6
+// [75.6], 512 x 6144 38.0 [86.6], 1024 x 6144 52.0 [86.2], 4096 x 1024 40.4
 // [81.0], 2048 x 6144 (a full round) [93.4], 4096 x 6144 [177.0; 128 x 192
-// 203.8, 256 x 128 187.8, 256 x 256 182.5].
-#define VD_LINEAR_SHAPES(X)       \
-  X(1, 2, 1, 1, 256, 6, 1, 12.0f) \
-  X(2, 2, 1, 1, 256, 5, 1, 14.0f) \
-  X(1, 4, 1, 1, 256, 3, 1, 15.2f) \
-  X(4, 2, 1, 1, 256, 3, 1, 16.6f) \
-  X(2, 2, 2, 2, 64, 4, 2, 20.0f)  \
-  X(2, 2, 2, 3, 64, 4, 2, 23.5f)  \
-  X(2, 4, 2, 2, 64, 4, 2, 28.0f)  \
-  X(4, 4, 2, 2, 64, 4, 4, 37.5f)  \
-  X(4, 2, 2, 6, 64, 3, 2, 52.5f)  \
-  X(4, 2, 4, 6, 64, 2, 2, 88.0f)
+// 203.8, 256 x 128 187.8, 256 x 256 182.5].  LATE, on the same box without
+// and with: 64 x 32 16.8 / 16.0, 64 x 128 30.2 / 29.7, 128 x 128 38.7 / 38.0, 128 x
+// 192 58.4 / 52.0; 64 x 64 20.4 / 21.1, 64 x 96 23.2 / 23.9, 256 x 192 178.7 / 185.1.
+// The same blocks as 32 x 32 x 16 steps are slower in every shape (256 x 192:
+// 198).
+#define VD_LINEAR_SHAPES(X)              \
+  X(1, 2, 1, 1, 256, 6, 1, false, 12.0f) \
+  X(2, 2, 1, 1, 256, 5, 1, false, 14.0f) \
+  X(1, 4, 1, 1, 256, 3, 1, false, 15.2f) \
+  X(4, 2, 1, 1, 256, 3, 1, true, 16.0f)  \
+  X(2, 2, 2, 2, 64, 4, 2, false, 20.0f)  \
+  X(2, 2, 2, 3, 64, 4, 2, false, 23.5f)  \
+  X(2, 4, 2, 2, 64, 4, 2, true, 27.5f)   \
+  X(4, 4, 2, 2, 64, 4, 4, true, 37.0f)   \
+  X(4, 2, 2, 6, 64, 3, 2, true, 51.0f)   \
+  X(4, 2, 4, 6, 64, 2, 2, false, 88.0f)
 
 // The launch of the shape with the least rounds x time of a round.  The choice
 // never reaches a value (the arithmetic above).
@@ -273,8 +288,8 @@ int run(const Call& x) {
       fn = f;
     }
   };
-#define VD_LINEAR_CONSIDER(wm, wn, xb, yb, bk, st, eu, us) \
-  consider(16 * wm * xb, 16 * wn * yb, us, &launch<Tile<wm, wn, xb, yb, bk, st, eu>>);
+#define VD_LINEAR_CONSIDER(wm, wn, xb, yb, bk, st, eu, late, us) \
+  consider(16 * wm * xb, 16 * wn * yb, us, &launch<Tile<wm, wn, xb, yb, bk, st, eu, late>>);
   VD_LINEAR_SHAPES(VD_LINEAR_CONSIDER)
 #undef VD_LINEAR_CONSIDER
   return fn(x);
