@@ -204,10 +204,11 @@ int vd_attn_forward_noalloc(const vd_attn* h, const vd_attn_batch* batch, void* 
  *           a plan launch, every workgroup derives its items from the lengths
  *           and the call's new tokens are written by this launch: the items
  *           write their own requests' rows, and further workgroups, after
- *           the items', those of the requests of the chunks phase.  When the
- *           call can have more items than the launch has workgroups (and its
- *           K/V stream past the caches: no shared_pages hint), a one-wavefront
- *           launch first zeroes a counter in the workspace, from which the
+ *           the items', those of the requests of the chunks phase.  In a call
+ *           of few items (each finds a compute unit of its own) eight
+ *           wavefronts share each out.  When the call can have more items
+ *           than the launch has workgroups (and its K/V stream past the
+ *           caches: no shared_pages hint), a one-wavefront launch first zeroes a counter in the workspace, from which the
  *           workgroups claim the items past their first.  A request with one
  *           split writes its output rows directly; otherwise each item writes
  *           a partial state;

@@ -22,11 +22,14 @@
 //                 layout; writes a partial state.  Whole 1024-key splits are
 //                 listed before the shorter last splits, and those by
 //                 decreasing length, so the shortest items fill the end of
-//                 the launch.
+//                 the launch.  In calls of few items the shared-out split
+//                 kernel runs each of them with eight wavefronts.
 //   chunk kernel  one workgroup (4 wavefronts x 32 columns) per (request,
 //                 KV head, 128 query-head rows) for longer chunks (prefill);
 //                 K/V tiles are staged in LDS and shared by the wavefronts;
 //                 the splits are folded in registers with the merge's fold.
+//                 In calls of few items the paired chunk kernel runs 64 rows
+//                 per workgroup, two splits at a time.
 //   merge kernel  folds the split partial states in ascending split order
 //                 and writes the output rows of the split-path requests.
 // The work decomposition differs between kernels; the operations applied to
@@ -3311,14 +3314,17 @@ int run_merge(const Params& P, hipStream_t s) {
 
 template <int D>
 int run_chunks(const Params& P, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr) {
-  // upper bound of the items, Hkv sum_r ceil(s_r G / cols) <= Hkv floor((T G +
-  // B (cols - 1)) / cols)
-  auto items = [&](int cols) {
-    return (int64_t)P.hkv * ((P.T * P.G + (int64_t)P.num_seqs * (cols - 1)) / cols);
+  // workgroups of items of `cols` rows: an upper bound of sum_r Hkv ceil(s_r G /
+  // cols) <= Hkv (ceil(T G / cols) + B), rounded up to a multiple of the dies
+  auto grid = [&](int cols) {
+    const int64_t n = (int64_t)P.hkv * ((P.T * P.G + cols - 1) / cols + P.num_seqs);
+    return (n + P.xcds - 1) / P.xcds * P.xcds;
   };
-  auto grid = [&](int64_t n) { return (n + P.xcds - 1) / P.xcds * P.xcds; };
-  const int64_t blocks = grid(items(kChunkCols));
+  const int64_t blocks = grid(kChunkCols);
   if (blocks > INT32_MAX) return VD_ERR_INVALID_ARG;
+  // the most paired items: Hkv floor((T G + B (cols - 1)) / cols)
+  const int64_t pairs =
+      (int64_t)P.hkv * ((P.T * P.G + (int64_t)P.num_seqs * (kPairCols - 1)) / kPairCols);
   // Paired items when every one of them finds a CU of its own and some context
   // is longer than a split: the chunk kernel then has at most half a
   // workgroup per CU, and runs a row's splits one after the other.  With more
@@ -3326,13 +3332,13 @@ int run_chunks(const Params& P, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent
   // runs two workgroups on a CU (calls, us, chunk kernel against pairs: a
   // 1000-token chunk at key 30000, 252 items of the chunk kernel, 748 / 910; 512
   // tokens, 128 items, 671 / 438; 64 tokens at key 8000, 16 items, 182 / 121).
-  if (P.inwave && P.max_splits > 1 && items(kPairCols) <= device_geometry().cus) {
+  if (P.inwave && P.max_splits > 1 && pairs <= device_geometry().cus) {
     constexpr size_t lds = chunk_pair_lds_bytes<D>();
     const auto kern = P.window > 0 ? &chunk_pair_kernel<D, true> : &chunk_pair_kernel<D, false>;
     static std::atomic<unsigned char> lds_set[2][kMaxDevices];
     if (set_lds_limit(reinterpret_cast<const void*>(kern), (int)lds, lds_set[P.window > 0]) != hipSuccess)
       return VD_ERR_LAUNCH;
-    hipExtLaunchKernelGGL(kern, dim3((unsigned)grid(items(kPairCols))), dim3(128 * kPairWaves),
+    hipExtLaunchKernelGGL(kern, dim3((unsigned)grid(kPairCols)), dim3(128 * kPairWaves),
                           (uint32_t)lds, s, e0, e1, 0, P);
     return launched();
   }

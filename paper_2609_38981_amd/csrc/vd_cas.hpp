@@ -82,9 +82,11 @@ __device__ __forceinline__ float fmax_(float a, float b) { return __builtin_fmax
 // half) of every pair of lanes l, l ^ 16 (l, l ^ 32) and the second the odd
 // row (upper half).  The two wait states before each swap are its hazard
 // after a vector-ALU write of either register.  Every lane of the wavefront
-// must be active (the callers' tile loops are wave-uniform).  Not volatile: the
-// results depend on the two registers alone, and a volatile statement would
-// keep the compiler from scheduling LDS reads across the softmax.
+// must be active (the callers' tile loops are wave-uniform; device inline
+// assembly is convergent, so the compiler moves it under no other condition).
+// Not volatile: the results depend on the two registers alone, and a volatile
+// statement would keep the compiler from scheduling LDS reads across the
+// softmax.
 __device__ __forceinline__ void swap_rows16(float& a, float& b) {
   asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
 }

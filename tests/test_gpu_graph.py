@@ -8,6 +8,8 @@ same workspace, and the workspace overwritten with 0xFF bytes.
   counter (a kernel, not a memset), so each replay claims from zero whatever
   the previous call or the overwrite left there.
 * The 8B decode batch (every item in the launch's first round).
+* A decode call of few items (a workgroup per split) and one prefill chunk
+  (paired splits; no split or merge launch), and the tiny call (no merge).
 * The allocation-free entry point (for callers that capture graphs and cannot
   allocate), whose workspace is the library's static scratch.
 The bits of a row depend only on its request (Section 5.3), so every replay
@@ -23,10 +25,20 @@ from tests import gpu_util as U
 
 pytestmark = pytest.mark.gpu
 
+
+
+def one_chunk():
+    p = W.make_prompt(W.LLAMA8B, 2300, 75, 0, q_window=64)
+    return W.place(W.LLAMA8B, [p], [W.Req(0, 2300, 64)], W.rng_for(75, 4))
+
+
 CALLS = {
     # 6 requests x 8 KV heads x 88-108 splits: about 4,900 split items
     "long-decode-d64-claims": (lambda: W.config4(batch=6, lo=90000, hi=110000,
                                                  shape=W.Shape(16, 8, 64)), False),
+    "decode8b-few": (lambda: W.config2(batch=2, lo=1500, hi=1900), False),
+    "one-chunk": (one_chunk, False),
+    "tiny": (lambda: W.config1(), False),
     "decode8b": (lambda: W.config2(), False),
     "decode8b-noalloc": (lambda: W.config2(), True),
 }
