@@ -208,8 +208,9 @@ int vd_attn_forward_noalloc(const vd_attn* h, const vd_attn_batch* batch, void* 
  *           of few items (each finds a compute unit of its own) eight
  *           wavefronts share each out.  When the call can have more items
  *           than the launch has workgroups (and its K/V stream past the
- *           caches: no shared_pages hint), a one-wavefront launch first zeroes a counter in the workspace, from which the
- *           workgroups claim the items past their first.  A request with one
+ *           caches: no shared_pages hint), a one-wavefront launch first
+ *           zeroes a counter in the workspace, from which the workgroups
+ *           claim the items past their first.  A request with one
  *           split writes its output rows directly; otherwise each item writes
  *           a partial state;
  *   chunks: rows of requests with s_r * (Hq / Hkv) > 32 -- one work item per
