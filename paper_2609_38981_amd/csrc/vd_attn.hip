@@ -2923,7 +2923,7 @@ __global__ __launch_bounds__(256) void kv_write_kernel(const uint16_t* knew, con
       const int rows = lrows[x];
       const int64_t src = ((t0 + ltok[x]) * hkv + h) * D + 8 * dc, stride = (int64_t)hkv * D;
       u16x8 kv[4], vv[4];
-  #pragma unroll
+#pragma unroll
       for (int i = 0; i < 4; ++i) {
         kv[i] = i < rows ? *reinterpret_cast<const u16x8*>(knew + src + i * stride) : zero8();
         vv[i] = i < rows ? *reinterpret_cast<const u16x8*>(vnew + src + i * stride) : zero8();
@@ -2932,23 +2932,23 @@ __global__ __launch_bounds__(256) void kv_write_kernel(const uint16_t* knew, con
       const int s0 = (int)(lslot[x] % kPage);
       // K block: element (slot, d) at ((d / 8) * 16 + slot) * 8 + d % 8
       uint16_t* kd = kpool + blk + ((int64_t)dc * kPage + s0) * 8;
-  #pragma unroll
+#pragma unroll
       for (int i = 0; i < 4; ++i)
         if (i < rows) *reinterpret_cast<u16x8*>(kd + 8 * i) = kv[i];
       // V block: element (slot, d) at ((d / 16) * 4 + slot / 4) * 64 + (d % 16) * 4 + slot % 4
       uint16_t* vd = vpool + blk + ((dc / 2) * 4 + s0 / 4) * 64 + (dc % 2) * 32 + s0 % 4;
       if (rows == 4) {  // a whole group (s0 % 4 == 0): 2 d per 16-byte store
-  #pragma unroll
+#pragma unroll
         for (int e = 0; e < 8; e += 2) {
           const u16x8 o = {vv[0][e],     vv[1][e],     vv[2][e],     vv[3][e],
                            vv[0][e + 1], vv[1][e + 1], vv[2][e + 1], vv[3][e + 1]};
           *reinterpret_cast<u16x8*>(vd + 4 * e) = o;
         }
       } else {
-  #pragma unroll
+#pragma unroll
         for (int i = 0; i < 4; ++i)
           if (i < rows)
-  #pragma unroll
+#pragma unroll
             for (int e = 0; e < 8; ++e) vd[4 * e + i] = vv[i][e];
       }
     }
