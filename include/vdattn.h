@@ -214,8 +214,9 @@ int vd_attn_forward_noalloc(const vd_attn* h, const vd_attn_batch* batch, void* 
  *           split writes its output rows directly; otherwise each item writes
  *           a partial state;
  *   chunks: rows of requests with s_r * (Hq / Hkv) > 32 -- one work item per
- *           (request, KV head, 128 query-head rows), or per 64 rows when those
- *           number at most one per compute unit; folds the splits in
+ *           (request, KV head, 128 query-head rows), or, in calls of such
+ *           rows only, per 64 rows when those number at most one per compute
+ *           unit; folds the splits in
  *           registers and writes their output rows;
  *   merge:  folds the partial states of the split-phase rows of requests
  *           with more than one split, in ascending split order, and writes

@@ -3325,14 +3325,19 @@ int run_chunks(const Params& P, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent
   // the most paired items: Hkv floor((T G + B (cols - 1)) / cols)
   const int64_t pairs =
       (int64_t)P.hkv * ((P.T * P.G + (int64_t)P.num_seqs * (kPairCols - 1)) / kPairCols);
-  // Paired items when every one of them finds a CU of its own and some context
-  // is longer than a split: the chunk kernel then has at most half a
-  // workgroup per CU, and runs a row's splits one after the other.  With more
+  // Paired items when every one of them finds a CU of its own and some chunk's
+  // context is longer than a split: the chunk kernel then has at most half a
+  // workgroup per CU, and runs a row's splits one after the other.  The
+  // longest context is a chunk's for sure only when the call has no split-path
+  // rows (split_cols 0); beside decodes the chunks may have one split each,
+  // which pairs run no faster with half the wavefronts (calls, us, before and
+  // with pairs: 400 tokens from key 0 and 4 decodes 48.8 / 51.9, 64 tokens at
+  // key 900 and a decode 61.4 / 63.7).  With more
   // items a second round of pairs takes as long as the chunk kernel, which
   // runs two workgroups on a CU (calls, us, chunk kernel against pairs: a
   // 1000-token chunk at key 30000, 252 items of the chunk kernel, 748 / 910; 512
   // tokens, 128 items, 671 / 438; 64 tokens at key 8000, 16 items, 182 / 121).
-  if (P.inwave && P.max_splits > 1 && pairs <= device_geometry().cus) {
+  if (P.inwave && P.split_cols == 0 && P.max_splits > 1 && pairs <= device_geometry().cus) {
     constexpr size_t lds = chunk_pair_lds_bytes<D>();
     const auto kern = P.window > 0 ? &chunk_pair_kernel<D, true> : &chunk_pair_kernel<D, false>;
     static std::atomic<unsigned char> lds_set[2][kMaxDevices];
