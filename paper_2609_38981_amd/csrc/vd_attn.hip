@@ -3059,8 +3059,10 @@ bool plans_inwave(const vd_attn_batch* b) { return b->num_seqs <= kInWaveMaxSeqs
 // max_q_len of them (one request alone, or chunks of one length).  The call's
 // requests then all take the chunk path, whatever their lengths say
 // (split_cols 0), and the split workgroups and the merge are not launched.
+// Only for a max_q_len with which the chunk kernel is launched: a query buffer
+// longer than the rows in use, or a request past the hint, meets the count too.
 bool all_chunks(const vd_attn* h, const vd_attn_batch* b) {
-  return plans_inwave(b) &&
+  return plans_inwave(b) && (int64_t)b->max_q_len * h->group > kSplitCols &&
          (b->total_q_tokens - (int64_t)(b->num_seqs - 1) * b->max_q_len) * h->group > kSplitCols;
 }
 

@@ -6,6 +6,7 @@ from __future__ import annotations
 import ctypes
 
 import pytest
+import torch
 
 from paper_2609_38981_amd import vdattn as V
 
@@ -213,4 +214,23 @@ def test_noalloc_host_checks(lib):
     e = V._Batch(0, 0, None, None, None, None, 0, None, None, 0, 0, 0, None, None, 0, None)
     assert lib.vd_attn_forward_noalloc(h, ctypes.byref(e), None, None) == 0        # nothing to do
     assert lib.vd_attn_forward_noalloc(None, ctypes.byref(b), fake, None) == -1
+    lib.vd_attn_destroy(h)
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="its pointers are not memory: without a "
+                    "device only the launches fail")
+@pytest.mark.parametrize("B,T,max_q", [(4, 64, 1), (1, 9, 1), (1, 16, 8), (64, 80, 1), (2, 41, 1),
+                                       (1, 40, 40), (8, 128, 16)])
+@pytest.mark.parametrize("append", [False, True])
+def test_a_call_with_rows_launches(lib, B, T, max_q, append):
+    """A call with query rows launches a kernel whatever total_q_tokens says of
+    max_q_len (a query buffer may be longer than the rows in use): without a
+    device it reports the failed launch, never VD_OK."""
+    rc, h = _create(lib)
+    fake = 0x10000
+    new = fake if append else None
+    b = V._Batch(B, T, fake, fake, fake, fake, 256, fake, fake, 4096, max_q, 4096, new, new, 0, None)
+    ws = ctypes.c_size_t()
+    lib.vd_attn_workspace_size(h, B, max_q, 4096, ctypes.byref(ws))
+    assert lib.vd_attn_forward(h, ctypes.byref(b), fake, fake, ws.value, None) == -4
     lib.vd_attn_destroy(h)

@@ -330,6 +330,41 @@ def test_calls_of_prefill_rows_only(shape, append):
     assert np.array_equal(got[:1], want)
 
 
+@pytest.mark.parametrize("append", [False, True], ids=["written", "append"])
+def test_query_buffer_longer_than_its_rows(append):
+    """Decode rows at the start of a longer query buffer (total_q_tokens past
+    cu_q_lens[B], max_q_len 1), and beside a request with more rows than
+    max_q_len (skipped): output, log-sum-exp and new tokens' slots as without
+    the further rows."""
+    shape = W.LLAMA8B
+    ps = [W.make_prompt(shape, n, 75, n, q_window=40) for n in (300, 1100, 2500, 60)]
+    attn = U.handle(shape)
+    rng = W.rng_for(75, 4)
+    cut = W.place(shape, ps, [W.Req(i, p.length, 1) for i, p in enumerate(ps)], rng)
+    past = W.place(shape, ps, [W.Req(i, p.length, 40 if i == 3 else 1) for i, p in enumerate(ps)], rng)
+    for call, rows, pad in ((cut, 4, 60), (past, 3, 0)):
+        alone = call.subcall(range(rows))
+        want = S.to_device(attn, alone, append=append, lse=True).batch
+        wo = attn.forward(want)
+        b = S.to_device(attn, call, append=append, lse=True).batch
+        b.q = torch.cat([b.q, b.q[:1].expand(pad, -1, -1)])
+        b.lse = torch.empty(b.q.shape[:2], dtype=torch.float32, device="cuda")
+        if append:
+            b.k_new = torch.cat([b.k_new, b.k_new[:1].expand(pad, -1, -1)])
+            b.v_new = torch.cat([b.v_new, b.v_new[:1].expand(pad, -1, -1)])
+        b.max_q_len = 1
+        got = attn.forward(b)
+        assert np.array_equal(S.bits_of(got)[:rows], S.bits_of(wo))
+        assert torch.equal(b.lse[:rows], want.lse)
+        for r in range(rows):  # the requests' pages, in the call's and in their own placement
+            n = alone.reqs[r].n
+            for pool in ("k_pool", "v_pool"):
+                x = getattr(b, pool).view(torch.int16).view(b.num_pages, -1)
+                y = getattr(want, pool).view(torch.int16).view(want.num_pages, -1)
+                k = (n + 15) // 16
+                assert torch.equal(x[b.page_table[r, :k].long()], y[want.page_table[r, :k].long()])
+
+
 SHARE_SHAPES = [W.LLAMA8B, W.LLAMA70B, W.Shape(8, 8, 64), W.Shape(21, 3, 64, window=700),
                 W.Shape(32, 8, 128, window=1100)]
 
