@@ -2871,88 +2871,93 @@ __global__ __launch_bounds__(64) void validate_kernel(const int32_t* cu, const i
 }
 
 // ---------------------------------------------------------------------------
-// KV write: a workgroup writes the rows of kWriteTokens consecutive tokens.
-// Tokens whose slots follow each other inside an aligned group of 4 slots are
-// written together, by the group's first token (the leader), which may lie up
-// to 3 tokens before the group's last: in the pool layout 4 such slots are 64
-// contiguous bytes per 8 d of K and of V, so a thread -- one per (leader, KV
-// head, 8 consecutive d) -- moves 4 rows' 16-byte pieces of each with 16-byte
-// loads and stores, V transposed in registers.  Bound by HBM and, for a few
-// thousand tokens, by the chain slots -> rows -> stores of one launch.  One
-// thread per (token, head, 8 d), with eight 2-byte V stores each, took 25.6 us
-// for 4096 tokens (8 KV heads, d 128: 33.5 MB moved, 1.3 TB/s); this takes 12.1
-// us (2.8 TB/s).
+// KV write: the rows of kWriteTokens consecutive tokens (a window, grid x) by
+// gridDim.y workgroups.  Four tokens whose slots are an aligned group of 4 are
+// written together by the first one's threads: in the pool layout such slots are
+// 64 contiguous bytes per 8 d of K and of V, so a thread -- one per (whole group
+// or single token, KV head, 8 consecutive d) -- moves 4 rows' 16-byte pieces of
+// each with 16-byte loads and stores, V transposed in registers.  A token outside
+// a whole group has threads of its own (eight 2-byte V stores each).  Bound by
+// HBM and, below a few thousand tokens, by the chain slots -> rows -> stores of one
+// launch, as long as a thread has one piece to move: a window's pieces go to as
+// many workgroups as hold them (vd_kv_write has the rule).  us per call back to
+// back in a graph; one thread per (token, head, 8 d) / one workgroup per window
+// with runs of 2 or 3 tokens in one thread / this: 8 KV heads of 128, 64 single
+// tokens 3.7 / 7.3 / 3.4, 1024 9.1 / 11.6 / 9.4, 4096 in a row 33.7 / 10.8 /
+// 10.1 (33.5 MB moved); 32 KV heads, 64 single tokens 4.3 / 22.9 / 4.5, 512 25.0
+// / 29.0 / 15.8; 1 KV head, 16384 verify tokens (runs of 4 from anywhere) 8.9 /
+// 13.8 / 9.3.
 // ---------------------------------------------------------------------------
 constexpr int kWriteTokens = 8;
+constexpr int kWriteWgs = 4096;  // most workgroups of a launch that splits windows
 
 template <int D>
 __global__ __launch_bounds__(256) void kv_write_kernel(const uint16_t* knew, const uint16_t* vnew,
                                                        const int64_t* slots, int64_t ntok,
                                                        uint16_t* kpool, uint16_t* vpool,
                                                        int64_t num_pages, int hkv) {
-  __shared__ int64_t lslot[kWriteTokens];  // per leader: its slot,
-  __shared__ int ltok[kWriteTokens];       // its token in the window, and
-  __shared__ int lrows[kWriteTokens];      // the rows it writes (1 .. 4)
+  __shared__ int64_t lslot[kWriteTokens];  // per unit (group or token): its first slot,
+  __shared__ int ltok[kWriteTokens];       // its first token in the window (~: a whole group)
   const int lane = __lane_id();
   const int per_tok = hkv * (D / 8);
   for (int64_t t0 = (int64_t)blockIdx.x * kWriteTokens; t0 < ntok;
        t0 += (int64_t)gridDim.x * kWriteTokens) {
-    // lane i: the slot of token t0 - 1 + i (-1: none, or not to be written),
-    // through the 3 tokens after the window
-    const int64_t t = t0 - 1 + lane;
-    int64_t slot = lane < kWriteTokens + 4 && t >= 0 && t < ntok ? slots[t] : -1;
+    // lane i: the slot of token t0 - 4 + i (-1: none, or not to be written),
+    // from the 4 tokens before the window through the 3 after it
+    const int64_t t = t0 - 4 + lane;
+    int64_t slot = lane < kWriteTokens + 7 && t >= 0 && t < ntok ? slots[t] : -1;
     if (slot >= num_pages * kPage) slot = -1;
     const int64_t prev = __shfl_up((long long)slot, 1, 64);
-    // written with the token before it
-    const bool joins = lane > 0 && slot >= 0 && prev >= 0 && slot == prev + 1 && slot % 4 != 0;
-    const unsigned long long joined = __ballot(joins);
-    const bool leads = lane >= 1 && lane <= kWriteTokens && slot >= 0 && !joins;
-    const unsigned long long leaders = __ballot(leads);
-    if (leads) {  // every wavefront writes the same values
-      const int x = __popcll(leaders & ((1ull << lane) - 1));
-      const unsigned long long after = ~(joined >> (lane + 1));
+    const uint64_t follows = __ballot(lane > 0 && slot >= 0 && prev >= 0 && slot == prev + 1);
+    // slots 4 k .. 4 k + 3 in a row, from this lane's
+    const bool whole = slot >= 0 && slot % 4 == 0 && lane < 61 && ((follows >> (lane + 1)) & 7) == 7;
+    const uint64_t wholes = __ballot(whole);
+    const uint64_t inner = wholes << 1 | wholes << 2 | wholes << 3;  // their other three tokens
+    const bool unit = lane >= 4 && lane < kWriteTokens + 4 && slot >= 0 && !((inner >> lane) & 1);
+    const uint64_t units = __ballot(unit);
+    if (unit) {  // every wavefront writes the same values
+      const int x = __popcll(units & ((1ull << lane) - 1));
       lslot[x] = slot;
-      ltok[x] = lane - 1;
-      lrows[x] = 1 + __builtin_ctzll(after | 8);  // joins of at most 3 tokens follow
+      ltok[x] = whole ? ~(lane - 4) : lane - 4;
     }
     __syncthreads();
-    const int total = __popcll(leaders) * per_tok;
-    for (int q = threadIdx.x; q < total; q += 256) {
+    const int total = __popcll(units) * per_tok;
+    for (int q = blockIdx.y * 256 + threadIdx.x; q < total; q += 256 * gridDim.y) {
       const int x = q / per_tok, hd = q % per_tok;
       const int h = hd / (D / 8), dc = hd % (D / 8);
-      const int rows = lrows[x];
-      const int64_t src = ((t0 + ltok[x]) * hkv + h) * D + 8 * dc, stride = (int64_t)hkv * D;
-      u16x8 kv[4], vv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        kv[i] = i < rows ? *reinterpret_cast<const u16x8*>(knew + src + i * stride) : zero8();
-        vv[i] = i < rows ? *reinterpret_cast<const u16x8*>(vnew + src + i * stride) : zero8();
-      }
+      const int tok = ltok[x];
+      const int64_t src = ((t0 + (tok < 0 ? ~tok : tok)) * hkv + h) * D + 8 * dc;
       const int64_t blk = (lslot[x] / kPage * hkv + h) * (int64_t)(kPage * D);
       const int s0 = (int)(lslot[x] % kPage);
       // K block: element (slot, d) at ((d / 8) * 16 + slot) * 8 + d % 8
       uint16_t* kd = kpool + blk + ((int64_t)dc * kPage + s0) * 8;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (i < rows) *reinterpret_cast<u16x8*>(kd + 8 * i) = kv[i];
       // V block: element (slot, d) at ((d / 16) * 4 + slot / 4) * 64 + (d % 16) * 4 + slot % 4
       uint16_t* vd = vpool + blk + ((dc / 2) * 4 + s0 / 4) * 64 + (dc % 2) * 32 + s0 % 4;
-      if (rows == 4) {  // a whole group (s0 % 4 == 0): 2 d per 16-byte store
+      if (tok < 0) {
+        const int64_t stride = (int64_t)hkv * D;
+        u16x8 kv[4], vv[4];
 #pragma unroll
-        for (int e = 0; e < 8; e += 2) {
+        for (int i = 0; i < 4; ++i) {
+          kv[i] = *reinterpret_cast<const u16x8*>(knew + src + i * stride);
+          vv[i] = *reinterpret_cast<const u16x8*>(vnew + src + i * stride);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *reinterpret_cast<u16x8*>(kd + 8 * i) = kv[i];
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {  // 2 d per 16-byte store
           const u16x8 o = {vv[0][e],     vv[1][e],     vv[2][e],     vv[3][e],
                            vv[0][e + 1], vv[1][e + 1], vv[2][e + 1], vv[3][e + 1]};
           *reinterpret_cast<u16x8*>(vd + 4 * e) = o;
         }
       } else {
+        const u16x8 kv = *reinterpret_cast<const u16x8*>(knew + src);
+        const u16x8 vv = *reinterpret_cast<const u16x8*>(vnew + src);
+        *reinterpret_cast<u16x8*>(kd) = kv;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (i < rows)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) vd[4 * e + i] = vv[i][e];
+        for (int e = 0; e < 8; ++e) vd[4 * e] = vv[e];
       }
     }
-    __syncthreads();  // the leaders' list is free for the next window
+    __syncthreads();  // the units' list is free for the next window
   }
 }
 
@@ -3565,8 +3570,16 @@ int vd_kv_write(const vd_attn* h, const void* k_new, const void* v_new,
   if (!aligned(k_new, 16) || !aligned(v_new, 16) || !aligned(slot_mapping, 8) ||
       !aligned(k_pool, 16) || !aligned(v_pool, 16))
     return VD_ERR_INVALID_ARG;
-  const int64_t windows = (num_tokens + kWriteTokens - 1) / kWriteTokens;
-  const dim3 grid((unsigned)std::min<int64_t>(windows, 1 << 20)), block(256);
+  // A workgroup per 256 pieces (token, head, 8 d) of a window, fewer when the
+  // windows alone fill the chip: past about 4096 workgroups the ones a window's
+  // whole groups leave without work cost more than the others gain.  us with at
+  // most 1024, 2048, 4096 and 8192 workgroups, 32 KV heads of 128: 2048 tokens in
+  // a row 22.2, 22.1, 19.6, 19.4; 16384 verify tokens 391, 390, 376, 510.
+  const int64_t per_tok = (int64_t)h->hkv * (h->d / 8);
+  const int64_t windows = std::min<int64_t>((num_tokens + kWriteTokens - 1) / kWriteTokens, 1 << 20);
+  const int64_t parts = std::max<int64_t>(
+      1, std::min<int64_t>((kWriteTokens * per_tok + 255) / 256, kWriteWgs / windows));
+  const dim3 grid((unsigned)windows, (unsigned)parts), block(256);
   const uint16_t* kn = static_cast<const uint16_t*>(k_new);
   const uint16_t* vn = static_cast<const uint16_t*>(v_new);
   uint16_t* kp = static_cast<uint16_t*>(k_pool);

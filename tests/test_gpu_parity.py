@@ -54,6 +54,55 @@ def test_kv_write_runs(shape, first):
     check_kv_write(shape, rng, num_pages, slots)
 
 
+@pytest.mark.parametrize("heads,tokens", [(1, 9), (3, 40), (32, 7), (32, 64), (32, 4100)])
+def test_kv_write_windows(heads, tokens):
+    """Windows of 8 tokens split over workgroups: less than one's work, several
+    workgroups per window, and more windows than may be split in full; single
+    tokens, runs of 2 and 3 and whole 4-slot groups in the same windows."""
+    rng = np.random.default_rng(heads + tokens)
+    num_pages = tokens // 8 + 20
+    free = rng.permutation(num_pages * 16 // 4)  # 4-slot groups
+    slots = np.concatenate([4 * g + np.arange(4)[a:b] for g, (a, b) in zip(
+        free, [((0, 4), (0, 4), (1, 3), (3, 4), (0, 3), (2, 4), (0, 1))[i]
+               for i in rng.integers(0, 7, len(free))])])[:tokens]
+    assert len(slots) == tokens
+    check_kv_write(W.Shape(heads, heads, 128), rng, num_pages, slots.astype(np.int64))
+
+
+def test_kv_write_of_a_few_tokens_takes_no_longer_than_one():
+    """The write of a small decode batch (16 tokens of 32 KV heads, 0.5 MB) is
+    one launch's latency, like that of one token: its pieces are spread over the
+    chip.  (A workgroup per 8 tokens: 22 us against 4.4; bound of 2.5x on the
+    smallest of several graph replays.)"""
+    shape = W.Shape(32, 32, 128)
+    attn = U.handle(shape)
+    num_pages = 64
+    kp, vp = attn.new_pool(num_pages), attn.new_pool(num_pages)
+    k = torch.zeros(16, 32, 128, dtype=torch.bfloat16, device="cuda")
+
+    def time(tokens):
+        slots = (torch.arange(tokens) * 48 + 5).cuda()
+        attn.kv_write(k[:tokens], k[:tokens], slots, kp, vp, num_pages)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            for _ in range(50):
+                attn.kv_write(k[:tokens], k[:tokens], slots, kp, vp, num_pages)
+        best = float("inf")
+        for _ in range(8):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            g.replay()
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best * 20.0  # us per call
+
+    one, few = time(1), time(16)
+    U.say("  kv_write: 1 token %.2f us, 16 tokens %.2f us" % (one, few))
+    assert few < 2.5 * one
+
+
 def check_kv_write(shape, rng, num_pages, slots):
     attn = U.handle(shape)
     T = len(slots)
