@@ -224,8 +224,9 @@ int vd_attn_forward_noalloc(const vd_attn* h, const vd_attn_batch* batch, void* 
  *           most one split (1024).
  * When total_q_tokens and max_q_len leave every request more rows than the
  * split phase takes (one request alone, chunks of one length; at most 256
- * requests), all of them run in the chunks phase: the splits phase then only
- * writes the new tokens and the merge launches nothing. */
+ * requests) and a row has at most 32 splits, the chunks phase also does the merge
+ * (of requests that have fewer rows all the same: total_q_tokens past
+ * cu_q_lens[B]) and the merge launches nothing. */
 int vd_attn_forward_plan(const vd_attn* h, const vd_attn_batch* batch, void* workspace,
                          size_t workspace_bytes, hipStream_t stream);
 int vd_attn_forward_splits(const vd_attn* h, const vd_attn_batch* batch, void* out,

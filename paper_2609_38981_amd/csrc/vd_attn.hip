@@ -90,6 +90,11 @@ struct Params {
   int wide;
   // the split workgroups derive their items from the lengths (no plan launch)
   int inwave;
+  // every request has chunk-path rows by the host's sizes (all_chunks)
+  int expect_chunks;
+  // ... and there is no merge launch: the chunk launch lists every request, and
+  // its workgroups of a split-path request fold that request's partial states
+  int fold_short;
   float* lse;  // optional [T, Hq] log-sum-exp output
   // shared-prefix pass (calls with the shared_pages hint): the plan launch
   // finds groups of adjacent requests whose page tables start with the same
@@ -1275,8 +1280,8 @@ __device__ __forceinline__ bool inwave_split_item(const Params& P, int vb, Split
 
 // Chunk items without a plan launch (at most kInWaveMaxSeqs requests): the
 // same one-round-trip read of the lengths, and the items of the plan's chunk
-// list -- per KV head, every q-tile of 128 query-head rows of every request
-// on the chunk path -- with XCD-contiguous ranges.  A workgroup's run time
+// list -- per KV head, every q-tile of `cols` query-head rows of every request
+// on the chunk path (fold_short: of every request) -- with XCD-contiguous ranges.  A workgroup's run time
 // grows with its last row's position, so when at most kLongestFirstReqs
 // requests are on the chunk path the list takes them longest first
 // (decreasing n, ties by index) and a request's q-tiles from its last: the
@@ -1305,7 +1310,7 @@ __device__ __forceinline__ bool inwave_chunk_item(const Params& P, int cols, int
     if (64 * c + lane < P.num_seqs) {
       const Req Rl = make_req(P, cq0[c], cq1[c], cn[c]);
       const int ncols = Rl.s * P.G;
-      if (Rl.valid && ncols > P.split_cols) cnt[c] = (ncols + cols - 1) / cols;
+      if (Rl.valid && (P.fold_short || ncols > P.split_cols)) cnt[c] = (ncols + cols - 1) / cols;
     }
     incl[c] = wave_scan_dpp(cnt[c]);
     per_head += __builtin_amdgcn_readlane(incl[c], 63);
@@ -1374,7 +1379,7 @@ __device__ __forceinline__ bool inwave_chunk_item(const Params& P, int cols, int
   qt = uni(off);
   R = make_req(P, q0, q1, n);
   const int ncols = R.s * P.G;
-  return r < P.num_seqs && g < P.hkv && R.valid && ncols > P.split_cols &&
+  return r < P.num_seqs && g < P.hkv && R.valid && (P.fold_short || ncols > P.split_cols) &&
          qt < (ncols + cols - 1) / cols;
 }
 
@@ -2069,6 +2074,60 @@ __device__ __forceinline__ void order_pv_reads() {
   __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
 }
 
+// The merge of a split-path request's rows by one 256-thread workgroup of the
+// chunk launch (fold_short): a thread per (column, 4 consecutive d), the partial
+// states in ascending split order with the merge kernels' operations, KB of
+// them loaded at a time.  Bound by the latency of those rounds.
+constexpr int kShortFold = 32;  // the most splits of a row folded this way
+
+template <int D>
+__device__ __forceinline__ void fold_short_rows(const Params& P, int r, int g, const Req& R) {
+  constexpr int KB = 16;
+  if (request_splits(R, P.window) == 1) return;          // written by the split kernel
+  if (P.casc && folds_prefix(R, P.casc_seq[r])) return;  // written by its last split's items
+  const int items = R.s * P.G * (D / 4);
+  for (int id = threadIdx.x; id < items; id += 256) {
+    const int c = id / (D / 4), d = 4 * (id % (D / 4));
+    // the row's splits: from the one holding its window start through its own
+    const int pr = R.n - R.s + c / P.G;
+    const int klo = window_lo(pr, P.window) / kSplitKeys;
+    const int kp = pr / kSplitKeys + 1 - klo;
+    const int64_t p0 = ((int64_t)(r * P.hkv + g) * P.ws_cols + c) * P.max_splits + klo;
+    float M = P.ws_m[p0], Z = P.ws_z[p0];
+    f32x4 W = *reinterpret_cast<const f32x4*>(P.ws_u + p0 * D + d);
+    for (int k0 = 1; k0 < kp; k0 += KB) {
+      float mk[KB], zk[KB];
+      f32x4 uk[KB];
+#pragma unroll
+      for (int k = 0; k < KB; ++k) {
+        if (k0 + k < kp) {
+          const int64_t p = p0 + k0 + k;
+          mk[k] = P.ws_m[p];
+          zk[k] = P.ws_z[p];
+          uk[k] = *reinterpret_cast<const f32x4*>(P.ws_u + p * D + d);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < KB; ++k) {
+        if (k0 + k < kp) {
+          const FoldScalars f = fold_scalars(M, Z, mk[k], zk[k]);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) W[i] = fold_value(W[i], uk[k][i], f);
+          M = f.M;
+          Z = f.Z;
+        }
+      }
+    }
+    const float rho = final_scale(Z);
+    u16x4 o;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = bf16_out(W[i] * rho);
+    const int64_t row = (int64_t)(R.q0 + c / P.G) * P.hq + g * P.G + c % P.G;
+    *reinterpret_cast<u16x4*>(P.out + row * D + d) = o;
+    if (P.lse && d == 0) P.lse[row] = final_lse(M, Z);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // chunk kernel: one workgroup (4 wavefronts x 32 columns) per
 // (request, KV head, 128 query-head rows).  The request's K/V tiles stream
@@ -2264,6 +2323,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   Req R;
   if (P.inwave) {
     if (!inwave_chunk_item(P, kChunkCols, g, r, qt, R)) return;
+    if (R.s * P.G <= P.split_cols) {
+      fold_short_rows<D>(P, r, g, R);
+      return;
+    }
   } else {
     const int per_head = P.off_chunk[P.num_seqs];
     const int total = per_head * P.hkv;
@@ -2450,6 +2513,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   int g, r, qt;
   Req R;
   if (!inwave_chunk_item(P, COLS, g, r, qt, R)) return;
+  if (R.s * P.G <= P.split_cols) {
+    fold_short_rows<D>(P, r, g, R);
+    return;
+  }
   const int ncols = R.s * P.G;
   const int c0 = qt * COLS;
   const int cend = min(ncols, c0 + COLS);
@@ -3059,13 +3126,12 @@ bool needs_chunks_params(const Params& P) { return (int64_t)P.max_q * P.G > kSpl
 // chunk workgroups derive their items from the lengths.
 bool plans_inwave(const vd_attn_batch* b) { return b->num_seqs <= kInWaveMaxSeqs; }
 
-// Every request has rows for the chunk path: no request has more than
-// max_q_len rows, so even the shortest holds total_q_tokens - (num_seqs - 1)
-// max_q_len of them (one request alone, or chunks of one length).  The call's
-// requests then all take the chunk path, whatever their lengths say
-// (split_cols 0), and the split workgroups and the merge are not launched.
-// Only for a max_q_len with which the chunk kernel is launched: a query buffer
-// longer than the rows in use, or a request past the hint, meets the count too.
+// By the host's sizes every request has rows for the chunk path: no request has
+// more than max_q_len rows, so even the shortest holds total_q_tokens -
+// (num_seqs - 1) max_q_len of them (one request alone, or chunks of one length),
+// and the chunk kernel is launched.  A request that the device finds short all
+// the same (total_q_tokens is a buffer's length, or a captured call is replayed
+// with other lengths) still runs in the split launch.
 bool all_chunks(const vd_attn* h, const vd_attn_batch* b) {
   return plans_inwave(b) && (int64_t)b->max_q_len * h->group > kSplitCols &&
          (b->total_q_tokens - (int64_t)(b->num_seqs - 1) * b->max_q_len) * h->group > kSplitCols;
@@ -3082,11 +3148,10 @@ bool fuses_write(const vd_attn* h, const vd_attn_batch* b) {
 }
 
 // The shared-prefix pass runs for calls with the shared_pages hint: at most
-// kCascMaxSeqs requests, no sliding window, contexts of more than one split, and
-// requests that may be on the split path (its members).
+// kCascMaxSeqs requests, no sliding window, contexts of more than one split.
 bool cascades(const vd_attn* h, const vd_attn_batch* b) {
-  return b->shared_pages != 0 && h->window == 0 && b->num_seqs >= 2 && !all_chunks(h, b) &&
-         b->num_seqs <= kCascMaxSeqs && b->max_context_len > kSplitKeys &&
+  return b->shared_pages != 0 && h->window == 0 && b->num_seqs >= 2 && b->num_seqs <= kCascMaxSeqs &&
+         b->max_context_len > kSplitKeys &&
          b->total_q_tokens * h->group <= INT32_MAX;
 }
 
@@ -3098,6 +3163,13 @@ bool needs_plan(const vd_attn* h, const vd_attn_batch* b) {
 
 int split_nb(const vd_attn* h, int32_t max_q_len) {
   return (int64_t)max_q_len * h->group <= 16 ? 1 : 2;
+}
+
+// The most splits a row folds: every split through the longest context, or
+// with a window of w keys the splits from the one holding p - w + 1 to the
+// one holding p, at most floor((w - 1) / 1024) + 2.
+int max_fold(const Params& P) {
+  return P.window > 0 ? std::min(P.max_splits, (P.window - 1) / kSplitKeys + 2) : P.max_splits;
 }
 
 Params make_params(const vd_attn* h, const vd_attn_batch* b, void* out, const void* ws) {
@@ -3125,7 +3197,8 @@ Params make_params(const vd_attn* h, const vd_attn_batch* b, void* out, const vo
   P.max_q = b->max_q_len;
   P.max_ctx = b->max_context_len;
   P.max_splits = (b->max_context_len + kSplitKeys - 1) / kSplitKeys;
-  P.split_cols = all_chunks(h, b) ? 0 : 16 * split_nb(h, b->max_q_len);
+  P.split_cols = 16 * split_nb(h, b->max_q_len);
+  P.expect_chunks = all_chunks(h, b);
   P.ws_cols = ws_cols(h, b->max_q_len);
   // wide items when every request is on the split path and some may have
   // more than 16 rows (max_q G in 17 .. 32); a call with chunk-path rows keeps
@@ -3142,6 +3215,14 @@ Params make_params(const vd_attn* h, const vd_attn_batch* b, void* out, const vo
   P.knew = static_cast<const uint16_t*>(b->k_new);
   P.vnew = static_cast<const uint16_t*>(b->v_new);
   P.inwave = plans_inwave(b);
+  // Calls that expect chunk rows only have no merge launch: the chunk launch
+  // folds what the split launch left, usually nothing (us with a merge launch
+  // and without: a prompt of 1500 tokens 55.9, 54.1; 8 chunks of 128 tokens at
+  // 1500 keys 50.1, 48.5; 4 decodes of 16000 keys in room for 64 tokens each 48.0,
+  // 46.8).  Past kShortFold splits a request's fold by one workgroup takes
+  // longer than the launch (one decode of 100000 keys, 98 splits: 78.6 with,
+  // 82.2 without; 32 splits are two rounds of loads).
+  P.fold_short = P.expect_chunks && P.max_splits > 1 && max_fold(P) <= kShortFold;
   P.lse = b->lse;
   P.fuse_write = fuses_write(h, b);
   P.append_wgs = 0;  // set by the split launch
@@ -3203,8 +3284,7 @@ int run_splits(const Params& P0, bool stream_kv, hipStream_t s, hipEvent_t e0 = 
   // 128); a multiple of the dies
   const Geometry geo = device_geometry();
   const int64_t cap = (P.wide && D == 128 ? 8 : 16) * (int64_t)geo.cus;
-  const int64_t split_wgs =
-      P.split_cols == 0 ? 0 : (std::min(items, cap) + geo.xcds - 1) / geo.xcds * geo.xcds;
+  const int64_t split_wgs = (std::min(items, cap) + geo.xcds - 1) / geo.xcds * geo.xcds;
   // the chunk-path requests' new tokens: a workgroup per unit up to the cap
   // (an upper bound of the units: every request's page runs number at most
   // s / 16 + 2, times the KV heads), dispatched after the split workgroups
@@ -3214,7 +3294,6 @@ int run_splits(const Params& P0, bool stream_kv, hipStream_t s, hipEvent_t e0 = 
     append = (std::min(units, cap) + geo.xcds - 1) / geo.xcds * geo.xcds;
   }
   P.append_wgs = (int)append;
-  if (split_wgs + append == 0) return record_pair(s, e0, e1);
   // Calls that can have more items than workgroups take the later ones from
   // a counter in the workspace header, when the items derive their own slots
   // and the K/V stream past the caches (with shared pages, each die keeps its
@@ -3235,7 +3314,7 @@ int run_splits(const Params& P0, bool stream_kv, hipStream_t s, hipEvent_t e0 = 
   // 2000 (256 items) 33.9 / 32.0, 4 of 1700 verifying 4 tokens at 8 query heads
   // per KV head 44.4 / 22.5; in two rounds, 16 of 4000 keys, 45.9 / 64.3; two
   // tiles (the smallest call) 8.2 / 8.6.
-  if (P.inwave && !P.casc && split_wgs > 0 && append == 0 && shared_items <= geo.cus &&
+  if (P.inwave && !P.casc && append == 0 && shared_items <= geo.cus &&
       P.max_ctx > 2 * kTileKeys) {
     P.wide = 0;  // 16-row items
     P.claim = nullptr;
@@ -3245,7 +3324,7 @@ int run_splits(const Params& P0, bool stream_kv, hipStream_t s, hipEvent_t e0 = 
     return launched();
   }
   P.claim = nullptr;
-  if (P.inwave && stream_kv && !P.casc && split_wgs > 0 && item_bound > split_wgs) {
+  if (P.inwave && stream_kv && !P.casc && item_bound > split_wgs) {
     P.claim = P.casc_hdr + kClaimWord;
     hipLaunchKernelGGL(zero_claim_kernel, dim3(1), dim3(64), 0, s, P.claim);
   }
@@ -3293,15 +3372,10 @@ int run_split_phase(const Params& P, bool stream_kv, hipStream_t s, hipEvent_t e
 
 template <int D>
 int run_merge(const Params& P, hipStream_t s) {
-  // contexts of one split are written by the split kernel, chunk-path rows by
-  // the chunk kernel
-  if (P.max_splits <= 1 || P.split_cols == 0) return VD_OK;
+  // contexts of one split are written by the split kernel
+  if (P.max_splits <= 1 || P.fold_short) return VD_OK;
   const int64_t cols = P.ws_cols;
-  // the most splits a row folds: every split through the longest context, or
-  // with a window of w keys the splits from the one holding p - w + 1 to the
-  // one holding p, at most floor((w - 1) / 1024) + 2
-  const int fold = P.window > 0 ? std::min(P.max_splits, (P.window - 1) / kSplitKeys + 2)
-                                : P.max_splits;
+  const int fold = max_fold(P);
   if (fold <= kShortMerge) {
     const int64_t threads = (int64_t)P.num_seqs * P.hkv * cols * (D / 4);
     const int64_t blocks = (threads + 255) / 256;
@@ -3335,8 +3409,8 @@ int run_chunks(const Params& P, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent
   // Paired items when every one of them finds a CU of its own and some chunk's
   // context is longer than a split: the chunk kernel then has at most half a
   // workgroup per CU, and runs a row's splits one after the other.  The
-  // longest context is a chunk's for sure only when the call has no split-path
-  // rows (split_cols 0); beside decodes the chunks may have one split each,
+  // longest context is a chunk's for sure only when every request has chunk-path
+  // rows (expect_chunks); beside decodes the chunks may have one split each,
   // which pairs run no faster with half the wavefronts (calls, us, before and
   // with pairs: 400 tokens from key 0 and 4 decodes 48.8 / 51.9, 64 tokens at
   // key 900 and a decode 61.4 / 63.7).  With more
@@ -3344,7 +3418,7 @@ int run_chunks(const Params& P, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent
   // runs two workgroups on a CU (calls, us, chunk kernel against pairs: a
   // 1000-token chunk at key 30000, 252 items of the chunk kernel, 748 / 910; 512
   // tokens, 128 items, 671 / 438; 64 tokens at key 8000, 16 items, 182 / 121).
-  if (P.inwave && P.split_cols == 0 && P.max_splits > 1 && pairs <= device_geometry().cus) {
+  if (P.expect_chunks && P.max_splits > 1 && pairs <= device_geometry().cus) {
     constexpr size_t lds = chunk_pair_lds_bytes<D>();
     const auto kern = P.window > 0 ? &chunk_pair_kernel<D, true> : &chunk_pair_kernel<D, false>;
     static std::atomic<unsigned char> lds_set[2][kMaxDevices];

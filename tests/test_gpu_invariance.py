@@ -307,10 +307,10 @@ def test_paired_chunks_equal_chunks(shape, n, s):
 @pytest.mark.parametrize("shape", [W.LLAMA8B, W.TINY], ids=["d128", "d64"])
 @pytest.mark.parametrize("append", [False, True], ids=["written", "append"])
 def test_calls_of_prefill_rows_only(shape, append):
-    """Calls whose sizes rule the split path out (one chunk; chunks of one
-    length) run without it: the same bits as beside a decode row, new tokens
-    written or handed over; and a request with fewer rows than total_q_tokens
-    and max_q_len promise still gets its output."""
+    """Calls whose sizes leave every request chunk-path rows (one chunk; chunks
+    of one length): the same bits as beside a decode row, new tokens written or
+    handed over; and a request with fewer rows than total_q_tokens and max_q_len
+    promise still gets its output."""
     rng = W.rng_for(72, 4)
     ps = [W.make_prompt(shape, n, 72, i, q_window=60) for i, n in enumerate([1100, 700, 60, 300])]
     decode = [W.Req(3, 300, 1)]
@@ -328,6 +328,54 @@ def test_calls_of_prefill_rows_only(shape, append):
     b.max_q_len = 40
     got = S.bits_of(attn.forward(b))
     assert np.array_equal(got[:1], want)
+
+
+CAPACITY_SHAPES = [W.LLAMA8B, W.Shape(14, 2, 64), W.Shape(8, 8, 64), W.Shape(32, 8, 128, window=1500)]
+
+
+@pytest.mark.parametrize("shape", CAPACITY_SHAPES, ids=["d128-g4", "d64-g7", "d64-g1", "d128-window"])
+@pytest.mark.parametrize("append", [False, True], ids=["written", "append"])
+@pytest.mark.parametrize("shared", [False, True], ids=["own", "shared"])
+def test_short_requests_in_a_call_sized_for_chunks(shape, append, shared):
+    """Decode and verify rows, alone and beside a chunk, in a call whose
+    total_q_tokens and max_q_len leave room for chunks (a captured call's): they
+    run in the split launch like in a call of their own size (the splits phase
+    alone writes the rows of one split), and output and log-sum-exp are the
+    same, folded by the paired chunk kernel's launch, by the chunk kernel's (more
+    room) and, with more splits than those fold, by the merge."""
+    ns = [1, 60, 1024, 1025, 2500, 5000, 3000]
+    attn = U.handle(shape)
+    for last, room in ((40, 40), (40, 100), (34816, 40)):  # last request's keys: up to 34 splits
+        ps = [W.make_prompt(shape, n, 76, n, q_window=40) for n in ns + [last]]
+        if shared:  # the prompts of 2500 and 5000 keys begin with the same pages
+            ps[5] = W.make_prompt(shape, ns[5], 76, 1, q_window=40, prefix=ps[4], prefix_len=2048)
+        reqs = [W.Req(i, p.length, min(p.length, s)) for i, (p, s) in enumerate(
+            zip(ps, [1, 4, 1, 2, 1, 3, 40, 4]))]
+        call = W.place(shape, ps, reqs, W.rng_for(76, 4))
+        want, lse = U.gpu_run(call, append=append, with_lse=True)
+        b = S.to_device(attn, call, append=append, lse=True, shared_pages=shared).batch
+        T, pad = call.total_q_tokens, room * len(reqs) - call.total_q_tokens
+
+        def longer(x):
+            return torch.cat([x, x[:1].expand(pad, *x.shape[1:])])
+
+        b.q, b.lse, b.max_q_len = longer(b.q), longer(b.lse), room
+        if append:
+            b.k_new, b.v_new = longer(b.k_new), longer(b.v_new)
+        ws = attn.new_workspace(len(reqs), room, b.max_context_len)
+        out = torch.full_like(b.q, float("nan"))
+        attn.forward_plan(b, ws)
+        attn.forward_splits(b, out, ws)
+        single = [r for r, q in enumerate(reqs) if q.n <= 1024 and q.s * shape.group <= 32]
+        for r in single:
+            row = call.row_of(r, reqs[r].n - reqs[r].s)
+            got = S.bits_of(out)[row:row + reqs[r].s]
+            assert np.array_equal(got, want[row:row + reqs[r].s]), reqs[r]
+        assert len(single) >= 3
+        attn.forward_chunks(b, out, ws)
+        attn.forward_merge(b, out, ws)
+        assert np.array_equal(S.bits_of(out)[:T], want)
+        assert np.array_equal(b.lse[:T].cpu().numpy(), lse)
 
 
 @pytest.mark.parametrize("append", [False, True], ids=["written", "append"])
