@@ -232,12 +232,22 @@ struct Call {
   hipStream_t stream;
 };
 
+// Workgroups for the output tiles of bm x bn (M, N > 0), a multiple of the dies, or
+// -1 when a grid cannot hold them: the runtime counts a launch's threads in 32
+// bits, and a larger grid wraps.
+int64_t grid_blocks(const Call& x, int bm, int bn, int threads, int xcds) {
+  const int64_t tiles_m = (x.M - 1) / bm + 1, tiles_n = (x.N - 1) / bn + 1;
+  if (tiles_m > UINT32_MAX / tiles_n) return -1;
+  const int64_t blocks = (tiles_m * tiles_n + xcds - 1) / xcds * xcds;
+  return blocks * threads <= UINT32_MAX ? blocks : -1;
+}
+
 template <class T>
 int launch(const Call& x) {
-  const int64_t tiles_m = (x.M + T::BM - 1) / T::BM, tiles_n = ((int64_t)x.N + T::BN - 1) / T::BN;
+  const int64_t tiles_m = (x.M - 1) / T::BM + 1, tiles_n = (x.N - 1) / T::BN + 1;
   const Geometry geo = device_geometry();
-  const int64_t blocks = (tiles_m * tiles_n + geo.xcds - 1) / geo.xcds * geo.xcds;
-  if (tiles_m > INT32_MAX || blocks > INT32_MAX) return VD_ERR_INVALID_ARG;
+  const int64_t blocks = grid_blocks(x, T::BM, T::BN, T::kThreads, geo.xcds);
+  if (blocks < 0) return VD_ERR_INVALID_ARG;
   static std::atomic<unsigned char> lds_set[kMaxDevices];
   if (set_lds_limit(reinterpret_cast<const void*>(&linear_kernel<T>), T::kLds, lds_set) != hipSuccess)
     return VD_ERR_LAUNCH;
@@ -274,25 +284,27 @@ int launch(const Call& x) {
   X(4, 2, 2, 6, 64, 3, 2, true, 51.0f)   \
   X(4, 2, 4, 6, 64, 2, 2, false, 88.0f)
 
-// The launch of the shape with the least rounds x time of a round.  The choice
+// The launch of the shape with the least rounds x time of a round, of those whose
+// grid can be launched (a small tile's cannot for 2^29 rows).  The choice
 // never reaches a value (the arithmetic above).
 int run(const Call& x) {
-  const int cus = device_geometry().cus;
+  const Geometry geo = device_geometry();
   float best = 0.0f;
   int (*fn)(const Call&) = nullptr;
-  auto consider = [&](int bm, int bn, float round_us, int (*f)(const Call&)) {
-    const int64_t tiles = ((x.M + bm - 1) / bm) * (((int64_t)x.N + bn - 1) / bn);
-    const float t = (float)((tiles + cus - 1) / cus) * round_us;
+  auto consider = [&](int bm, int bn, int threads, float round_us, int (*f)(const Call&)) {
+    if (grid_blocks(x, bm, bn, threads, geo.xcds) < 0) return;
+    const int64_t tiles = ((x.M - 1) / bm + 1) * ((x.N - 1) / bn + 1);
+    const float t = (float)((tiles + geo.cus - 1) / geo.cus) * round_us;
     if (!fn || t < best) {
       best = t;
       fn = f;
     }
   };
 #define VD_LINEAR_CONSIDER(wm, wn, xb, yb, bk, st, eu, late, us) \
-  consider(16 * wm * xb, 16 * wn * yb, us, &launch<Tile<wm, wn, xb, yb, bk, st, eu, late>>);
+  consider(16 * wm * xb, 16 * wn * yb, 64 * wm * wn, us, &launch<Tile<wm, wn, xb, yb, bk, st, eu, late>>);
   VD_LINEAR_SHAPES(VD_LINEAR_CONSIDER)
 #undef VD_LINEAR_CONSIDER
-  return fn(x);
+  return fn ? fn(x) : VD_ERR_INVALID_ARG;
 }
 
 }  // namespace

@@ -135,6 +135,8 @@ def test_linear_rejects_before_launch(lib):
                dict(a=0), dict(b=0), dict(lda=32), dict(ldb=32), dict(lda=68), dict(ldb=68),
                dict(a=fake + 8), dict(b=fake + 8)):
         assert call(**kw) == -1, kw
+    # more rows than any launch covers
+    assert call(M=2**31 + 1, N=1, K=0) == -1 and call(M=2**62, N=2**30, ldc=2**30, K=0) == -1
     # K must be a multiple of the 64-wide step
     assert call(K=96, lda=96, ldb=96) == -2
 

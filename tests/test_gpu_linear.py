@@ -149,6 +149,18 @@ def test_linear_random_shapes(case):
         M, N, K, lda, err, len(sub), len(cols)))
 
 
+@pytest.mark.parametrize("M,N", [(64 * 2**23 - 64, 1), (64 * 2**23 + 100, 1), (128 * 2**22 + 7, 3)])
+def test_linear_more_rows_than_a_small_tile_covers(M, N):
+    """2^29 rows: the grid of the tile shapes for few columns would pass 2^32
+    threads; every output is written all the same (K = 0: +0)."""
+    out = torch.full((M, N), 1.0, dtype=torch.bfloat16, device="cuda")
+    rc = V.load_library().vd_linear(None, 0, None, 0, out.data_ptr(), N, M, N, 0,
+                                    torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    flat = out.view(-1).view(torch.int16)
+    assert not any(bool(flat[i:i + 2**28].any()) for i in range(0, flat.numel(), 2**28))
+
+
 @pytest.mark.parametrize("M,N,K", [
     (15, 5000, 320),     # 16 x 32 tiles, a ragged last K step of 64
     (31, 6100, 192),     # 32 x 32, K shorter than one step
