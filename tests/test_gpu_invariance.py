@@ -13,6 +13,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_2609_38981_amd import staging as S
 from paper_2609_38981_amd import vdattn as V
 from paper_2609_38981_amd import workloads as W
@@ -304,6 +305,48 @@ def test_paired_chunks_equal_chunks(shape, n, s):
     U.parity(alone, a, rows=[0, s // 2, s - 1])
 
 
+@pytest.mark.parametrize("shape", PAIR_SHAPES, ids=["d128-g4", "d64-g7", "d128-window"])
+@pytest.mark.parametrize("pages", [
+    [106],                      # one page of a tile in split 1
+    [128, 129, 130, 131, 190],  # a whole tile, split 2's first, and another page of it
+    [193],                      # the last, ragged tile (split 3)
+    [10, 106, 150, 193],        # both splits of each round
+], ids=["split1", "split2", "last", "all"])
+def test_chunks_read_invalid_pages_as_zeros(shape, pages):
+    """A prefill chunk whose table holds page ids outside the pool, in one split
+    of a round of the paired chunk kernel or in both, within a tile, over a whole
+    tile and in the last one: alone (paired) and beside enough other rows (the
+    chunk kernel) the same bits and log-sum-exp, and the oracle's values with
+    zeros in those pages."""
+    n, s = 3100, 257
+    p = W.make_prompt(shape, n, 77, n, q_window=s)
+    other = W.make_prompt(shape, 1200 * 32 // shape.num_q_heads, 77, 1)
+    alone = W.place(shape, [p], [W.Req(0, n, s)], W.rng_for(77, 4))
+    both = W.place(shape, [other, p], [W.Req(0, other.length, other.length), W.Req(1, n, s)],
+                   W.rng_for(77, 5))
+    attn = U.handle(shape)
+    got = []
+    for call in (alone, both):
+        b = S.to_device(attn, call, lse=True).batch
+        for i, pg in enumerate(pages):
+            b.page_table[-1, pg] = [-1, call.num_pages, -7, 2**31 - 1][i % 4]
+        out = S.bits_of(attn.forward(b))
+        got.append((out[-s:], b.lse.cpu().numpy()[-s:]))
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+    kp, vp = (x.copy() for x in alone.std_pool())
+    for x in (kp, vp):
+        x[alone.page_table[0, pages]] = 0
+    rows = [0, s // 2, s - 1]
+    ref = oracle.paged_attention(alone.q_bits(), alone.cu_q_lens, alone.context_lens, alone.page_table,
+                                 kp, vp, num_q_heads=shape.num_q_heads,
+                                 num_kv_heads=shape.num_kv_heads, head_dim=shape.head_dim,
+                                 page_size=shape.page_size, window=shape.window, rows=rows)[rows]
+    val = W.bf16_to_f32(got[0][0][rows]).astype(np.float64)
+    assert np.isfinite(val).all()
+    bound = np.minimum(U.TOL, U.REL_TOL * np.abs(ref).max(axis=-1, keepdims=True) + 1e-7)
+    assert (np.abs(val - ref) <= bound).all()
+
+
 @pytest.mark.parametrize("shape", [W.LLAMA8B, W.TINY], ids=["d128", "d64"])
 @pytest.mark.parametrize("append", [False, True], ids=["written", "append"])
 def test_calls_of_prefill_rows_only(shape, append):
@@ -427,6 +470,21 @@ def test_shared_out_splits_equal_splits(shape, append, s):
     slots, the same rows in a call of 70 requests (a wavefront per split):
     contexts of 3 tiles, at split and tile edges, with new tokens on both sides of
     a tile or split edge; and match the oracle."""
+    check_shared_out(shape, append, s)
+
+
+@pytest.mark.parametrize("shape,s", [
+    (W.Shape(8, 8, 64), 9), (W.Shape(8, 8, 64), 16), (W.Shape(16, 8, 128), 9), (W.Shape(16, 8, 128), 16),
+    (W.Shape(8, 8, 128), 17), (W.Shape(6, 6, 64), 32),
+], ids=["d64-g1-9", "d64-g1-16", "d128-g2-9", "d128-g2-16", "d128-g1-17", "d64-g1-32"])
+@pytest.mark.parametrize("append", [False, True], ids=["written", "append"])
+def test_shared_out_splits_of_many_rows(shape, append, s):
+    """The same for 9 to 16 new rows, which the split launch writes, and 17 to
+    32 rows of one query head per KV head, which the plan launch writes."""
+    check_shared_out(shape, append, s)
+
+
+def check_shared_out(shape, append, s):
     ns = [129, 577, 1024, 1025, 1026, 1100, 1984, 2050, 3071, 4096 + 64]
     ps = [W.make_prompt(shape, n, 73, n, q_window=s) for n in ns]
     ps += [W.make_prompt(shape, 100 + i, 73, i, q_window=1) for i in range(60)]
