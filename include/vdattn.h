@@ -137,7 +137,8 @@ typedef struct {
    * of every member (a request of the group with s_r * (Hq / Hkv) <= 32 whose rows all lie
    * past the shared splits), with the same operations per row as the request's own split
    * item, so the output bits do not change; the rest of each request's splits are read by
-   * its own split items.  Not with a sliding window, nor for more than 1024 requests.
+   * its own split items.  Not with a sliding window, for more than 1024 requests, or in a
+   * small call whose total_q_tokens and max_q_len leave every request chunks-phase rows.
    * Zero: every split is read by its request's items, K/V streamed past the caches with
    * non-temporal loads (the faster choice when each page is read once). */
   int32_t shared_pages;
@@ -214,19 +215,19 @@ int vd_attn_forward_noalloc(const vd_attn* h, const vd_attn_batch* batch, void* 
  *           split writes its output rows directly; otherwise each item writes
  *           a partial state;
  *   chunks: rows of requests with s_r * (Hq / Hkv) > 32 -- one work item per
- *           (request, KV head, 128 query-head rows), or, in calls of such
- *           rows only, per 64 rows when those number at most one per compute
- *           unit; folds the splits in
- *           registers and writes their output rows;
+ *           (request, KV head, 128 query-head rows), or per 64 rows in calls
+ *           (of at most 256 requests and of more than one split) whose
+ *           total_q_tokens and max_q_len leave every request such rows -- one
+ *           request alone, chunks of one length -- when those items number at
+ *           most one per compute unit; folds the splits in registers and
+ *           writes their output rows;
  *   merge:  folds the partial states of the split-phase rows of requests
  *           with more than one split, in ascending split order, and writes
  *           their output rows; launches nothing when max_context_len is at
  *           most one split (1024).
- * When total_q_tokens and max_q_len leave every request more rows than the
- * split phase takes (one request alone, chunks of one length; at most 256
- * requests) and a row has at most 32 splits, the chunks phase also does the merge
- * (of requests that have fewer rows all the same: total_q_tokens past
- * cu_q_lens[B]) and the merge launches nothing. */
+ * In a call of 64-row chunk items with at most 32 splits per row the chunks phase
+ * also does the merge, of requests whose rows are few all the same
+ * (total_q_tokens past cu_q_lens[B]), and the merge launches nothing. */
 int vd_attn_forward_plan(const vd_attn* h, const vd_attn_batch* batch, void* workspace,
                          size_t workspace_bytes, hipStream_t stream);
 int vd_attn_forward_splits(const vd_attn* h, const vd_attn_batch* batch, void* out,

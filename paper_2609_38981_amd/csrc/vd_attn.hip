@@ -90,10 +90,10 @@ struct Params {
   int wide;
   // the split workgroups derive their items from the lengths (no plan launch)
   int inwave;
-  // every request has chunk-path rows by the host's sizes (all_chunks)
-  int expect_chunks;
-  // ... and there is no merge launch: the chunk launch lists every request, and
-  // its workgroups of a split-path request fold that request's partial states
+  // the chunk launch is the paired kernel's (use_pairs)
+  int pairs;
+  // ... which lists every request, and whose workgroups of a split-path request
+  // fold that request's partial states in place of the merge launch
   int fold_short;
   float* lse;  // optional [T, Hq] log-sum-exp output
   // shared-prefix pass (calls with the shared_pages hint): the plan launch
@@ -1281,15 +1281,15 @@ __device__ __forceinline__ bool inwave_split_item(const Params& P, int vb, Split
 // Chunk items without a plan launch (at most kInWaveMaxSeqs requests): the
 // same one-round-trip read of the lengths, and the items of the plan's chunk
 // list -- per KV head, every q-tile of `cols` query-head rows of every request
-// on the chunk path (fold_short: of every request) -- with XCD-contiguous ranges.  A workgroup's run time
+// with more than `above` of them -- with XCD-contiguous ranges.  A workgroup's run time
 // grows with its last row's position, so when at most kLongestFirstReqs
 // requests are on the chunk path the list takes them longest first
 // (decreasing n, ties by index) and a request's q-tiles from its last: the
 // blocks of a die are dispatched in that order, which keeps the longest
 // items off the end of the launch.  Which workgroup computes a row never
 // changes its bits.
-__device__ __forceinline__ bool inwave_chunk_item(const Params& P, int cols, int& g, int& r, int& qt,
-                                                  Req& R) {
+__device__ __forceinline__ bool inwave_chunk_item(const Params& P, int cols, int above, int& g,
+                                                  int& r, int& qt, Req& R) {
   constexpr int C = kInWaveChunks;
   const int lane = __lane_id();
   int cq0[C], cq1[C], cn[C];
@@ -1310,7 +1310,7 @@ __device__ __forceinline__ bool inwave_chunk_item(const Params& P, int cols, int
     if (64 * c + lane < P.num_seqs) {
       const Req Rl = make_req(P, cq0[c], cq1[c], cn[c]);
       const int ncols = Rl.s * P.G;
-      if (Rl.valid && (P.fold_short || ncols > P.split_cols)) cnt[c] = (ncols + cols - 1) / cols;
+      if (Rl.valid && ncols > above) cnt[c] = (ncols + cols - 1) / cols;
     }
     incl[c] = wave_scan_dpp(cnt[c]);
     per_head += __builtin_amdgcn_readlane(incl[c], 63);
@@ -1379,7 +1379,7 @@ __device__ __forceinline__ bool inwave_chunk_item(const Params& P, int cols, int
   qt = uni(off);
   R = make_req(P, q0, q1, n);
   const int ncols = R.s * P.G;
-  return r < P.num_seqs && g < P.hkv && R.valid && (P.fold_short || ncols > P.split_cols) &&
+  return r < P.num_seqs && g < P.hkv && R.valid && ncols > above &&
          qt < (ncols + cols - 1) / cols;
 }
 
@@ -2322,11 +2322,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   int g, r, qt;
   Req R;
   if (P.inwave) {
-    if (!inwave_chunk_item(P, kChunkCols, g, r, qt, R)) return;
-    if (R.s * P.G <= P.split_cols) {
-      fold_short_rows<D>(P, r, g, R);
-      return;
-    }
+    if (!inwave_chunk_item(P, kChunkCols, P.split_cols, g, r, qt, R)) return;
   } else {
     const int per_head = P.off_chunk[P.num_seqs];
     const int total = per_head * P.hkv;
@@ -2482,7 +2478,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 // ---------------------------------------------------------------------------
 // paired chunk kernel: the chunk kernel's work for calls whose items would
-// leave CUs idle (run_chunks has the rule).  Two groups of two wavefronts per
+// leave CUs idle (use_pairs has the rule).  Two groups of two wavefronts per
 // workgroup run the same 64 query-head rows over alternate splits, each group
 // with its own LDS ring, one workgroup barrier per tile.  After each pair of
 // splits the groups exchange their states through LDS -- group 0 folds the
@@ -2512,7 +2508,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int window = WIN ? P.window : 0;
   int g, r, qt;
   Req R;
-  if (!inwave_chunk_item(P, COLS, g, r, qt, R)) return;
+  if (!inwave_chunk_item(P, COLS, P.fold_short ? 0 : P.split_cols, g, r, qt, R)) return;
   if (R.s * P.G <= P.split_cols) {
     fold_short_rows<D>(P, r, g, R);
     return;
@@ -3137,6 +3133,25 @@ bool all_chunks(const vd_attn* h, const vd_attn_batch* b) {
          (b->total_q_tokens - (int64_t)(b->num_seqs - 1) * b->max_q_len) * h->group > kSplitCols;
 }
 
+// Paired items when every one of them finds a CU of its own and some chunk's
+// context is longer than a split: the chunk kernel then has at most half a
+// workgroup per CU, and runs a row's splits one after the other.  The longest
+// context is a chunk's only when every request has chunk-path rows
+// (all_chunks); beside decodes the chunks may have one split each, which pairs
+// run no faster with half the wavefronts (calls, us, before and with pairs: 400
+// tokens from key 0 and 4 decodes 48.8 / 51.9, 64 tokens at key 900 and a decode
+// 61.4 / 63.7).  With more items a second round of pairs takes as long as the
+// chunk kernel, which runs two workgroups on a CU (calls, us, chunk kernel
+// against pairs: a 1000-token chunk at key 30000, 252 items of the chunk kernel,
+// 748 / 910; 512 tokens, 128 items, 671 / 438; 64 tokens at key 8000, 16 items,
+// 182 / 121).
+bool use_pairs(const vd_attn* h, const vd_attn_batch* b) {
+  // the most paired items: Hkv floor((T G + B (cols - 1)) / cols)
+  const int64_t rows = b->total_q_tokens * h->group + (int64_t)b->num_seqs * (kPairCols - 1);
+  return all_chunks(h, b) && b->max_context_len > kSplitKeys &&
+         h->hkv * (rows / kPairCols) <= device_geometry().cus;
+}
+
 // The split launch writes the call's new tokens when its workgroups plan for
 // themselves and no split-path request has more than kMaxNewRows query rows
 // (s * G <= 32 keeps s <= 16 for groups of two or more query heads): the
@@ -3148,10 +3163,22 @@ bool fuses_write(const vd_attn* h, const vd_attn_batch* b) {
 }
 
 // The shared-prefix pass runs for calls with the shared_pages hint: at most
-// kCascMaxSeqs requests, no sliding window, contexts of more than one split.
+// kCascMaxSeqs requests, no sliding window, contexts of more than one split.  Not
+// for a call that expects chunk rows only and has few splits: the plan and
+// shared-prefix launches cost it 10 us (8 chunks of 128 tokens at 1500 keys, 128
+// splits over the KV heads: 47.5 -> 59.2), and if its requests are short all the
+// same their own split items are as fast.  Requests in room for chunks, us with
+// the pass and without, 4-token rows at 8 query heads per KV head and 8 KV heads:
+// 192 splits 53.7 / 30.7, 1152 73.3 / 72.1, 2112 112 / 132; single rows of 32 KV
+// heads: 1152 82.3 / 77.3, 2304 87.6 / 116, 4224 190 / 232.
+constexpr int64_t kCascMinSplits = 1024;
+
 bool cascades(const vd_attn* h, const vd_attn_batch* b) {
-  return b->shared_pages != 0 && h->window == 0 && b->num_seqs >= 2 && b->num_seqs <= kCascMaxSeqs &&
-         b->max_context_len > kSplitKeys &&
+  const int64_t splits =
+      (int64_t)b->num_seqs * h->hkv * (((int64_t)b->max_context_len + kSplitKeys - 1) / kSplitKeys);
+  return b->shared_pages != 0 && h->window == 0 && b->num_seqs >= 2 &&
+         b->num_seqs <= kCascMaxSeqs && b->max_context_len > kSplitKeys &&
+         !(all_chunks(h, b) && splits <= kCascMinSplits) &&
          b->total_q_tokens * h->group <= INT32_MAX;
 }
 
@@ -3198,7 +3225,6 @@ Params make_params(const vd_attn* h, const vd_attn_batch* b, void* out, const vo
   P.max_ctx = b->max_context_len;
   P.max_splits = (b->max_context_len + kSplitKeys - 1) / kSplitKeys;
   P.split_cols = 16 * split_nb(h, b->max_q_len);
-  P.expect_chunks = all_chunks(h, b);
   P.ws_cols = ws_cols(h, b->max_q_len);
   // wide items when every request is on the split path and some may have
   // more than 16 rows (max_q G in 17 .. 32); a call with chunk-path rows keeps
@@ -3215,14 +3241,16 @@ Params make_params(const vd_attn* h, const vd_attn_batch* b, void* out, const vo
   P.knew = static_cast<const uint16_t*>(b->k_new);
   P.vnew = static_cast<const uint16_t*>(b->v_new);
   P.inwave = plans_inwave(b);
-  // Calls that expect chunk rows only have no merge launch: the chunk launch
-  // folds what the split launch left, usually nothing (us with a merge launch
-  // and without: a prompt of 1500 tokens 55.9, 54.1; 8 chunks of 128 tokens at
-  // 1500 keys 50.1, 48.5; 4 decodes of 16000 keys in room for 64 tokens each 48.0,
-  // 46.8).  Past kShortFold splits a request's fold by one workgroup takes
-  // longer than the launch (one decode of 100000 keys, 98 splits: 78.6 with,
-  // 82.2 without; 32 splits are two rounds of loads).
-  P.fold_short = P.expect_chunks && P.max_splits > 1 && max_fold(P) <= kShortFold;
+  P.pairs = use_pairs(h, b);
+  // With pairs there is no merge launch: the chunk launch folds what the split
+  // launch left, usually nothing (us with a merge launch and without: 100 tokens
+  // at key 2000 43.8, 42.3; 512 at 9000 144.8, 143.0; 4 decodes of 16000 keys in
+  // room for 64 tokens each 48.0, 46.8).  Past kShortFold splits a request's
+  // fold by one workgroup takes longer than the launch (one decode of 100000
+  // keys, 98 splits: 78.6 with, 82.2 without; 32 splits are two rounds of loads).
+  // (The same branch in the chunk kernel slowed its tile loop: the mixed batch
+  // 766 -> 781.)
+  P.fold_short = P.pairs && max_fold(P) <= kShortFold;
   P.lse = b->lse;
   P.fuse_write = fuses_write(h, b);
   P.append_wgs = 0;  // set by the split launch
@@ -3403,22 +3431,7 @@ int run_chunks(const Params& P, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent
   };
   const int64_t blocks = grid(kChunkCols);
   if (blocks > INT32_MAX) return VD_ERR_INVALID_ARG;
-  // the most paired items: Hkv floor((T G + B (cols - 1)) / cols)
-  const int64_t pairs =
-      (int64_t)P.hkv * ((P.T * P.G + (int64_t)P.num_seqs * (kPairCols - 1)) / kPairCols);
-  // Paired items when every one of them finds a CU of its own and some chunk's
-  // context is longer than a split: the chunk kernel then has at most half a
-  // workgroup per CU, and runs a row's splits one after the other.  The
-  // longest context is a chunk's for sure only when every request has chunk-path
-  // rows (expect_chunks); beside decodes the chunks may have one split each,
-  // which pairs run no faster with half the wavefronts (calls, us, before and
-  // with pairs: 400 tokens from key 0 and 4 decodes 48.8 / 51.9, 64 tokens at
-  // key 900 and a decode 61.4 / 63.7).  With more
-  // items a second round of pairs takes as long as the chunk kernel, which
-  // runs two workgroups on a CU (calls, us, chunk kernel against pairs: a
-  // 1000-token chunk at key 30000, 252 items of the chunk kernel, 748 / 910; 512
-  // tokens, 128 items, 671 / 438; 64 tokens at key 8000, 16 items, 182 / 121).
-  if (P.expect_chunks && P.max_splits > 1 && pairs <= device_geometry().cus) {
+  if (P.pairs) {
     constexpr size_t lds = chunk_pair_lds_bytes<D>();
     const auto kern = P.window > 0 ? &chunk_pair_kernel<D, true> : &chunk_pair_kernel<D, false>;
     static std::atomic<unsigned char> lds_set[2][kMaxDevices];

@@ -384,8 +384,8 @@ def test_short_requests_in_a_call_sized_for_chunks(shape, append, shared):
     total_q_tokens and max_q_len leave room for chunks (a captured call's): they
     run in the split launch like in a call of their own size (the splits phase
     alone writes the rows of one split), and output and log-sum-exp are the
-    same, folded by the paired chunk kernel's launch, by the chunk kernel's (more
-    room) and, with more splits than those fold, by the merge."""
+    same, folded by the paired chunk kernel's launch and, beside the chunk kernel
+    (more room) or with more splits than that folds, by the merge."""
     ns = [1, 60, 1024, 1025, 2500, 5000, 3000]
     attn = U.handle(shape)
     for last, room in ((40, 40), (40, 100), (34816, 40)):  # last request's keys: up to 34 splits
