@@ -107,7 +107,8 @@ void vd_attn_destroy(vd_attn* h);
 /* One call's packed inputs.  Pointers are device memory unless noted. */
 typedef struct {
   int32_t num_seqs;             /* B >= 0 */
-  int64_t total_q_tokens;       /* T = cu_q_lens[B] >= 0 */
+  int64_t total_q_tokens;       /* T = cu_q_lens[B] >= 0 (a longer q is read up to
+                                   cu_q_lens[B]; it may cost a slower choice of kernels) */
   const void* q;                /* [T, Hq, D] bf16, rows packed by request, i ascending */
   const int32_t* cu_q_lens;     /* [B + 1], cu[0] = 0, s_r = cu[r + 1] - cu[r] */
   const int32_t* context_lens;  /* [B], n_r (counts this call's own query tokens) */
@@ -116,8 +117,11 @@ typedef struct {
   const void* k_pool;           /* pools in the library layout (see vd_kv_write), */
   const void* v_pool;           /*   num_pages pages of Hkv page blocks each */
   int64_t num_pages;            /* >= 1 */
-  int32_t max_q_len;            /* HOST hint: >= every s_r (launch sizing only) */
-  int32_t max_context_len;      /* HOST hint: >= every n_r (launch sizing only) */
+  /* HOST hints, for launch sizes and the choice of kernels, never the values.  Loose ones
+   * cost speed: the kernels for calls of few items are chosen by what the hints allow (one
+   * decode of 1900 keys: 19 us, with max_context_len 131072 30). */
+  int32_t max_q_len;            /* >= every s_r */
+  int32_t max_context_len;      /* >= every n_r */
   /* Optional (NULL: none): the K and V of the call's own query rows, each [T, Hkv, D] bf16,
    * row t belonging to query row t.  Before any key is read, row t is written into the pool
    * at the slot that its logical position p has in its request's page table (the engine
@@ -299,12 +303,14 @@ int vd_kv_write(const vd_attn* h, const void* k_new, const void* v_new,
  * c: device [M rows of ldc] bf16 output (the first N values of a row written).
  * Each output element is one fp32 accumulation chain of v_mfma_f32_16x16x32_bf16 over K
  * in ascending 32-wide chunks starting from +0, cast to bf16 round-to-nearest-even: row m
- * of c is bit-identical for any M, any position of the row in a, and any strides.  The
- * tiling is fixed (it depends on nothing but the build); there is no split over K.
+ * of c is bit-identical for any M, any position of the row in a, and any strides.  The tile
+ * shape follows M, N and the device's compute units; no element's chain depends on it, and
+ * there is no split over K.
  * Requirements (else VD_ERR_UNSUPPORTED for K, VD_ERR_INVALID_ARG otherwise): K a multiple
  * of 64; when K > 0, lda, ldb >= K and multiples of 8 with a and b 16-byte aligned (K = 0:
  * a and b are not read and every output is +0); ldc >= N; c 2-byte aligned; M, N, K >= 0
- * (M = 0 or N = 0: nothing to do).  Launches on `stream` and
+ * (M = 0 or N = 0: nothing to do; VD_ERR_INVALID_ARG past 2^31 - 2048 rows, and for wider c
+ * past what one launch covers).  Launches on `stream` and
  * returns without waiting; allocates nothing.  Strides are in elements. */
 int vd_linear(const void* a, int64_t lda, const void* b, int64_t ldb, void* c, int64_t ldc,
               int64_t M, int32_t N, int32_t K, hipStream_t stream);

@@ -1219,7 +1219,8 @@ __device__ __forceinline__ bool inwave_split_item(const Params& P, int vb, Split
   } else {
     idx -= whole;
     // Items of each tile count t (1 .. 16) of the last partial splits, in an
-    // LDS histogram (the workgroup is this one wavefront); then lane l holds
+    // LDS histogram of the wavefront's own (the barriers are the workgroup's: every
+    // wavefront of one runs this for the same slot); then lane l holds
     // the items of the classes 16 .. 16 - l (longest first), and the first lane
     // whose count passes idx names the item's class.
     if (lane <= kTilesPerSplit) hist[lane] = 0;
@@ -1603,16 +1604,18 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NA == 1 || D
 // (run_splits has the rule), one workgroup of 8 wavefronts per item.  A
 // wavefront of the split kernel walks its split's tiles one after the other, one
 // tile's loads ahead: 25 us for the step of one request of 1900 keys, nearly all
-// of it latency.  Here every load of the split is in flight at once (256 KB
-// at head_dim 128), and the tiles' work is shared out: each wavefront runs Q.K
-// and the weights of two tiles, then one d-block of every P.V.  What is
+// of it latency.  Here a split's loads (512 KB at head_dim 128) are issued in two
+// batches: half of K (8 tiles, 128 KB) with V of tiles 0 .. 7 and the last two
+// (160 KB), then, after the first scores, the other half of K and V of tiles 8 ..
+// 13 (224 KB).  And the tiles' work is shared out: each wavefront runs Q.K and
+// the weights of two tiles, then one d-block of every P.V.  What is
 // sequential in the update is carried through LDS: the tile maxima give every
 // tile its running maximum (exact), the weights and alphas feed each d-block's
 // chain over the tiles in ascending order -- per column the operations of
 // split_item, in its order.  Much of what is left is the instruction fetch of
 // code that runs once: with the code for the request's end (new rows, masked
 // keys) in all 16 unrolled tiles instead of the last two the kernel was 100 KB
-// and the call took 23.4 us, now 18.5 (28.6 with the split kernel).
+// and the call took 23.4 us, now 18.9 (28.6 with the split kernel).
 // ---------------------------------------------------------------------------
 constexpr int kShareWaves = 8;
 
@@ -2018,7 +2021,7 @@ __global__ __launch_bounds__(64) void merge_long_kernel(Params P, int cols) {
 }
 
 // Issue order of a tile's LDS reads against its matrix instructions in the
-// chunk and shared-prefix kernels (scheduling hints only: every accumulator's
+// shared-prefix kernel's 16 x 16 x 32 steps (scheduling hints only: every accumulator's
 // chain of instructions, and so every bit, is the same).  Without them the
 // compiler keeps two K reads ahead of Q.K and one d-block's V reads ahead of
 // P.V, and waits on each.  Q.K: four of the tile's kPagesPerTile * D / 32 K
@@ -2255,7 +2258,9 @@ __device__ __forceinline__ void mask_tile(const Params& P, const int32_t* ptrow,
 
 // One wavefront's tile in the paired chunk kernel: Q.K, softmax and P.V of its
 // 32 columns over the staged tile T (first key j0); between(part) runs before
-// Q.K (0), before (1) and after (2) the softmax.
+// Q.K (0), before (1) and after (2) the softmax.  The chunk kernel has the same
+// step written out, where a call of this one spills 98 registers: a change of
+// one goes into the other.
 template <int D, bool WIN, class Between>
 __device__ __forceinline__ void chunk_tile(const uint16_t* T, const u16x8 (&qf)[D / 16],
                                            State32<D>& st, int j0, int pos, int lo, float c,
@@ -2264,9 +2269,11 @@ __device__ __forceinline__ void chunk_tile(const uint16_t* T, const u16x8 (&qf)[
   const int lane = __lane_id(), col = lane & 31, hf = lane >> 5;
   f32x16 acc[2];
   between(0);
-  // The two wavefronts of a SIMD belong to different workgroups; the one
-  // issuing matrix-core work gets the higher issue priority, the other's
-  // softmax fills the vector ALU around it.
+  // At one workgroup per CU a SIMD holds one wavefront, and no priority between
+  // wavefronts is meant: the instruction keeps the compiler from moving code
+  // across it.  Without the four, calls with a window of 4096 keys at head_dim 128
+  // took 4-5% longer (107.4 -> 111.5 us, 300 tokens at key 20000), the others
+  // up to 1.4% less.
   __builtin_amdgcn_s_setprio(2);
   // key 32 b + col: page 2 b + col / 16, slot col % 16
   const uint16_t* TK = T + (col / 16) * BLK + 128 * hf + 8 * (col % 16);
@@ -2417,7 +2424,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (kt % kTilesPerSplit == 0 || kt == kt_first) state32_init(st);
     const uint16_t* T = lds + buf * TILE;
     if (wave_pmax >= j0 && j0 + kTileKeys - 1 >= wave_lo) {
-      // (as a call of chunk_tile the compiler spills 98 registers in this kernel)
+      // (chunk_tile's step: as a call of it the compiler spills 98 registers)
       f32x16 acc[2];
       // The two wavefronts of a SIMD belong to different workgroups; the one
       // issuing matrix-core work gets the higher issue priority, the other's
@@ -3338,7 +3345,7 @@ int run_splits(const Params& P0, bool stream_kv, hipStream_t s, hipEvent_t e0 = 
       (int64_t)P.num_seqs * P.hkv * req_splits * ((int64_t)P.max_q * P.G > 16 ? 2 : 1);
   // Few items: a workgroup per item (one fits a CU at a time), when each finds
   // a CU of its own and contexts are longer than two tiles.  Calls, us, split
-  // kernel against shared-out items: 1 request of 1900 keys 28.6 / 18.5, 16 of
+  // kernel against shared-out items: 1 request of 1900 keys 28.6 / 18.9, 16 of
   // 2000 (256 items) 33.9 / 32.0, 4 of 1700 verifying 4 tokens at 8 query heads
   // per KV head 44.4 / 22.5; in two rounds, 16 of 4000 keys, 45.9 / 64.3; two
   // tiles (the smallest call) 8.2 / 8.6.

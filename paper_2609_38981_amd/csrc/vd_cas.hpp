@@ -255,7 +255,7 @@ __device__ __forceinline__ void tile_commit(State<D>& st, const TileWeights& w) 
 
 // ---------------------------------------------------------------------------
 // The same update on v_mfma_f32_32x32x16_bf16, for a wavefront with 32 columns
-// (chunk and shared-prefix kernels).  One 16x16x32 step equals two chained
+// (the chunk and paired chunk kernels).  One 16x16x32 step equals two chained
 // 32x32x16 steps, over operand elements k = 0..15 and then 16..31, in every
 // cell and bit (a probe on gfx950 pins it), so each dot product runs as a chain
 // of 32x32x16 steps in the same k order.  A 32x32x16 step keeps the matrix core
