@@ -1615,7 +1615,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NA == 1 || D
 // split_item, in its order.  Much of what is left is the instruction fetch of
 // code that runs once: with the code for the request's end (new rows, masked
 // keys) in all 16 unrolled tiles instead of the last two the kernel was 100 KB
-// and the call took 23.4 us, now 18.9 (28.6 with the split kernel).
+// and the call took 23.4 us, now 19.0 (28.6 with the split kernel).
 // ---------------------------------------------------------------------------
 constexpr int kShareWaves = 8;
 
@@ -3345,7 +3345,7 @@ int run_splits(const Params& P0, bool stream_kv, hipStream_t s, hipEvent_t e0 = 
       (int64_t)P.num_seqs * P.hkv * req_splits * ((int64_t)P.max_q * P.G > 16 ? 2 : 1);
   // Few items: a workgroup per item (one fits a CU at a time), when each finds
   // a CU of its own and contexts are longer than two tiles.  Calls, us, split
-  // kernel against shared-out items: 1 request of 1900 keys 28.6 / 18.9, 16 of
+  // kernel against shared-out items: 1 request of 1900 keys 28.6 / 19.0, 16 of
   // 2000 (256 items) 33.9 / 32.0, 4 of 1700 verifying 4 tokens at 8 query heads
   // per KV head 44.4 / 22.5; in two rounds, 16 of 4000 keys, 45.9 / 64.3; two
   // tiles (the smallest call) 8.2 / 8.6.
