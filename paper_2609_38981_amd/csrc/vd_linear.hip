@@ -267,7 +267,7 @@ int launch(const Call& x) {
 // [72.4], 100 x 6144 20.0 [74.4], 200 x 6144 23.3 [81.1], 300 x 6144 29.7
 // [75.6], 512 x 6144 38.0 [86.6], 1024 x 6144 52.0 [86.2], 4096 x 1024 40.4
 // [81.0], 2048 x 6144 (a full round) [93.4], 4096 x 6144 [177.0; 128 x 192
-// 203.8, 256 x 128 187.8, 256 x 256 182.5]; on another box the 16 x 64 shape, 16
+// 203.8, 256 x 128 187.8, 256 x 256 182.5]; on another card the 16 x 64 shape, 16
 // x 16000 20.4 [67.5] (its weights are 131 MB).  A round's time has a fixed part,
 // so the ratios follow K: with the table's times, at K = 1024, 1 x 6144 4.4
 // [18.7], 16 x 16000 5.1 [19.6], 48 x 6144 5.7 [20.7], 200 x 6144 8.3 [22.3], 512 x
@@ -275,7 +275,7 @@ int launch(const Call& x) {
 // 53.6 [53.7]; at K = 8192, 20.4 [130.8], 39.0 [132.8], 29.5 [133.0], 44.2
 // [136.1], 62.8 [137.3], 96.2 [141.2], 71.3 [140.0], 324 [320].  Of 283 calls over
 // 18 N x K (K 64 .. 14336, M 1 .. 8192) none is slower than with that one shape by
-// more than 3%.  LATE, on the same box without
+// more than 3%.  LATE, on one card without
 // and with: 64 x 32 16.8 / 16.0, 64 x 128 30.2 / 29.7, 128 x 128 38.7 / 38.0, 128 x
 // 192 58.4 / 52.0; 64 x 64 20.4 / 21.1, 64 x 96 23.2 / 23.9, 256 x 192 178.7 / 185.1.
 // The same blocks as 32 x 32 x 16 steps are slower in every shape (256 x 192:
